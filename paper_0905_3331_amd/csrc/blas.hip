@@ -3,7 +3,7 @@
 // One lane per lattice site (all 12 spin-colour components), so that the
 // per-site scaled 16-bit formats can be decoded and re-encoded in registers.
 // Grid: x over the sites, y over the RHS of the launch.  Every reduction
-// writes one FP64 partial per block; a single-block-per-RHS scalar kernel
+// writes one FP64 partial per wavefront; a single-block-per-RHS scalar kernel
 // sums the partials in a fixed order, which makes norms, inner products and
 // therefore iteration counts bit-reproducible from run to run and
 // independent of the batch an RHS is solved in.
@@ -36,11 +36,11 @@ __device__ __forceinline__ R site_norm2(const spinor<R> &s)
 // RHS of this block (grid y)
 #define BLOCK_RHS(rl) const int rhs = (rl).idx[blockIdx.y]
 
-#define WRITE_PARTIAL(ptr, pstride, part)                                   \
-    {                                                                       \
-        __shared__ double sh[BLAS_BLOCK / 64];                              \
-        const double s_ = block_sum(part, sh);                              \
-        if (threadIdx.x == 0) (ptr)[rhs * (pstride) + blockIdx.x] = s_;     \
+#define WRITE_PARTIAL(ptr, pstride, part)                                                             \
+    {                                                                                                 \
+        const double s_ = wave_sum(part);                                                             \
+        if ((threadIdx.x & 63) == 0)                                                                  \
+            (ptr)[rhs * (pstride) + (long)PARTS * blockIdx.x + (threadIdx.x >> 6)] = s_;              \
     }
 
 template <class F>
@@ -224,10 +224,16 @@ __global__ __launch_bounds__(BLAS_BLOCK) void k_accumulate(BatchView<SpF64> x, B
 
 constexpr int SC_THREADS = 1024;
 
+// the wavefronts' sums of n blocks: a block's in the order of its wavefronts
+// (as block_sum), the blocks in a fixed order
 __device__ __forceinline__ double det_sum(const double *partial, int n, double *sh)
 {
+    static_assert(PARTS == 4, "a block's partial sums are two 16-byte words");
     double v = 0.0;
-    for (int i = threadIdx.x; i < n; i += SC_THREADS) v += partial[i];
+    for (int i = threadIdx.x; i < n; i += SC_THREADS) {
+        const double2 a = ((const double2 *)partial)[2 * i], b = ((const double2 *)partial)[2 * i + 1];
+        v += (((0.0 + a.x) + a.y) + b.x) + b.y;
+    }
     return block_sum(v, sh);  // valid in thread 0
 }
 
@@ -283,6 +289,15 @@ __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const
         break;
     }
     if (publish) publish[rhs] = *s;
+}
+
+// out[i] = the sum of RHS rl.idx[i]
+__global__ __launch_bounds__(SC_THREADS) void k_sums(RhsList rl, const double *partial, long pstride, int nparts,
+                                                     double *out)
+{
+    __shared__ double sh[SC_THREADS / 64];
+    const double sum = det_sum(partial + rl.idx[blockIdx.x] * pstride, nparts, sh);
+    if (threadIdx.x == 0) out[blockIdx.x] = sum;
 }
 
 constexpr int SUM_THREADS = 1024;
@@ -396,6 +411,13 @@ hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long 
     if (rl.n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_scalar, dim3(rl.n), dim3(SC_THREADS), 0, st, op, rl, partial, pstride, nparts, s, tol2,
                        relative, skip_done ? 1 : 0, publish);
+    return hipGetLastError();
+}
+
+hipError_t launch_sums(const RhsList &rl, const double *partial, long pstride, int nparts, double *out, hipStream_t st)
+{
+    if (rl.n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_sums, dim3(rl.n), dim3(SC_THREADS), 0, st, rl, partial, pstride, nparts, out);
     return hipGetLastError();
 }
 

@@ -19,6 +19,15 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
     return s;
 }
 
+// Sum over a wavefront, valid in every lane; block_sum adds these of a block
+// in the order of its wavefronts
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
 __device__ __forceinline__ double block_max(double v, double *sh)
 {
 #pragma unroll

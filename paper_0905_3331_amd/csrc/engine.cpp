@@ -32,7 +32,7 @@ size_t engine_slot_bytes(long vh, int sloppy, int mode, bool nd)
 
 size_t engine_bytes(const Lattice *L, int sloppy, int cap, int mode, bool nd)
 {
-    return (size_t)cap * engine_slot_bytes(L->g.vh, sloppy, mode, nd) + (size_t)cap * 3 * L->pstride * sizeof(double) +
+    return (size_t)cap * engine_slot_bytes(L->g.vh, sloppy, mode, nd) + (size_t)cap * 3 * (L->pstride / PARTS) * sizeof(double) +
            (size_t)cap * sizeof(CgScalars);
 }
 

@@ -12,32 +12,22 @@ int hop_grid(long n)
     return (int)g;
 }
 
-// variant table: {order, SB}; the link loads are non-temporal for a single
-// RHS (each link is used once) and cached for a batch (each link is used once
-// per RHS of a group, from L2)
-struct HopVariant {
-    int ord;
-    bool sb;
-};
-static const HopVariant kVariants[HOP_VARIANTS] = {
-    {ORD_PLAIN, false}, {ORD_ZSLAB, false}, {ORD_ZSLAB, true}, {ORD_TSLAB, false}, {ORD_TSLAB, true},
-};
 
 bool hop_variant_valid(const Geom &g, int v)
 {
     if (v < 0 || v >= HOP_VARIANTS) return false;
-    if (kVariants[v].ord == ORD_ZSLAB) return g.LZ >= 8;
-    if (kVariants[v].ord == ORD_TSLAB) return g.T >= 8;
+    if (hop_order(v) == ORD_ZSLAB) return g.LZ >= 8;
+    if (hop_order(v) == ORD_TSLAB) return g.T >= 8;
     return true;
 }
 
 int hop_grid_variant(const Geom &g, int v, int lanes_per_site)
 {
     const long L = lanes_per_site;
-    if (!hop_variant_valid(g, v) || kVariants[v].ord == ORD_PLAIN) return hop_grid(L * g.vh);
+    if (!hop_variant_valid(g, v) || hop_order(v) == ORD_PLAIN) return hop_grid(L * g.vh);
     const long plane = (long)g.LY * g.XH;
     long per_xcd;
-    if (kVariants[v].ord == ORD_ZSLAB) {
+    if (hop_order(v) == ORD_ZSLAB) {
         const long zc = g.LZ / 8 + (g.LZ % 8 ? 1 : 0);
         per_xcd = (L * g.T * zc * plane + HOP_BLOCK - 1) / HOP_BLOCK;
     } else {

@@ -13,7 +13,7 @@
 // and accumulates the rebuilt four-spinor.  The epilogue forms
 // out = A * self + B * acc per spin half, which covers both factors of the
 // even/odd operator (eqs. (eo3), (eo4)) and the full-lattice operator, and
-// optionally reduces |out|^2 per block.
+// optionally reduces |out|^2 per wavefront.
 //
 // Work distribution: blocks of 256 lanes over consecutive eo indices (x
 // fastest, then y, z, t).  Hardware hands consecutive workgroups to the 8 XCDs
@@ -757,13 +757,13 @@ __global__ __launch_bounds__(HOP_BLOCK) void hop_kernel(HopArgs<SP, LK> a)
         }
     }
     if (NORM) {
-        // (doublets: the block's lanes hold both flavours, so the sum is over the doublet)
-        __shared__ double sh[G][HOP_BLOCK / 64];
+        // (doublets: the wavefront's lanes hold both flavours, so the sum is over the doublet)
 #pragma unroll
         for (int gi = 0; gi < G; gi++) {
             if (!live[gi]) continue;
-            const double s = block_sum(nrm[gi], sh[gi]);
-            if (threadIdx.x == 0) a.partial[(ND ? rhs[gi] >> 1 : rhs[gi]) * a.pstride + pidx] = s;
+            const double s = wave_sum(nrm[gi]);
+            if ((threadIdx.x & 63) == 0)
+                a.partial[(ND ? rhs[gi] >> 1 : rhs[gi]) * a.pstride + PARTS * pidx + (threadIdx.x >> 6)] = s;
         }
     }
 }
@@ -1257,13 +1257,12 @@ __global__ __launch_bounds__(HOP_BLOCK) void hop16_kernel(HopArgs<SP, L16R> a)
     }
     if (NORM) {
         // (doublets: each lane's value covers both flavours, so the sum is over the doublet)
-        __shared__ double sh[HOP_BLOCK / 64];
-        const double s = block_sum(nrm, sh);
-        if (threadIdx.x == 0) a.partial[(ND ? rhs >> 1 : rhs) * a.pstride + pidx] = s;
+        const long part = PARTS * pidx + (threadIdx.x >> 6);
+        const double s = wave_sum(nrm);
+        if ((threadIdx.x & 63) == 0) a.partial[(ND ? rhs >> 1 : rhs) * a.pstride + part] = s;
         if (TWO && two) {  // (uniform over the block)
-            __shared__ double sh2[HOP_BLOCK / 64];
-            const double s2 = block_sum(nrm2, sh2);
-            if (threadIdx.x == 0) a.partial[rhs_d * a.pstride + pidx] = s2;
+            const double s2 = wave_sum(nrm2);
+            if ((threadIdx.x & 63) == 0) a.partial[rhs_d * a.pstride + part] = s2;
         }
     }
 }
@@ -1407,6 +1406,11 @@ inline int rhs_group(const Geom &g, int prec, int n)
 // used format pairs); MULTI = true adds 2 RHS per lane for batches (the
 // FP32-arithmetic formats; FP64 lanes already use all 256 registers; 4 per
 // lane measured slower than 1 and 2).
+template <class SP, class LK>
+hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &self, const FieldDesc &out,
+                        const LinkDesc &lk, const OpParams &op, int epi, int sign, const RhsList &rl, double *partial,
+                        long pstride, const CgScalars *scal, int ord, int nblk, hipStream_t st, const CgFields *cg);
+
 template <class SP, class LK, bool ALL, bool MULTI>
 hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &self, const FieldDesc &out,
               const LinkDesc &lk, const OpParams &op, int epi, int sign, const RhsList &rl, double *partial,
@@ -1446,6 +1450,13 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
     if (ALL != hop_all_variants(in.prec, lk.fmt)) return hipErrorInvalidValue;  // tables out of step
     int variant = tu.variant;
     if (!ALL || !hop_variant_valid(g, variant)) variant = 0;
+    if constexpr (ALL) {
+        if (rl.n == 1 && !op.nd && hop_takes_split(g, in.prec, lk.fmt)) {
+            if (epi != EPI_K1 && !self.data) return hipErrorInvalidValue;
+            return launch_split<SP, LK>(g, out_par, in, self, out, lk, op, epi, sign, rl, partial, pstride, scal,
+                                        hop_order(variant), hop_grid_variant(g, variant), st, cg);
+        }
+    }
     // the divisors and site-term table of a batched 16-bit launch of ntup tuples
     auto batch16 = [&](int ntup) {
         if constexpr (SP::coded && __is_same(LK, L16R)) {
@@ -1559,12 +1570,16 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
             return hipGetLastError();
         }
     }
+    // (a single FP64 or FP32 field went to the split kernel)
 #define GOV(ORD, SB)                                                          \
     do {                                                                      \
-        if (nt)                                                               \
-            go_w<SP, LK, true, ORD, SB, 1>(a, s, n, ep, grid, block, lds, st);    \
-        else                                                                  \
-            go_w<SP, LK, false, ORD, SB, 1>(a, s, n, ep, grid, block, lds, st);   \
+        if constexpr (SP::coded) {                                            \
+            if (nt) {                                                         \
+                go_w<SP, LK, true, ORD, SB, 1>(a, s, n, ep, grid, block, lds, st); \
+                break;                                                        \
+            }                                                                 \
+        }                                                                     \
+        go_w<SP, LK, false, ORD, SB, 1>(a, s, n, ep, grid, block, lds, st);   \
     } while (0)
     switch (variant) {
     case 1: GOV(ORD_ZSLAB, false); break;

@@ -1,0 +1,11 @@
+// hop_split_b16.hip -- instantiations of the split half-sweep for one spinor format.
+#include "hop_split.h"
+
+namespace tmq {
+
+template hipError_t launch_split<SpB16, L16R>(const Geom &, int, const FieldDesc &, const FieldDesc &,
+                                                const FieldDesc &, const LinkDesc &, const OpParams &, int, int,
+                                                const RhsList &, double *, long, const CgScalars *, int, int,
+                                                hipStream_t, const CgFields *);
+
+}  // namespace tmq

@@ -130,6 +130,9 @@ struct CgScalars {
 
 constexpr int HOP_BLOCK = 256;
 constexpr int BLAS_BLOCK = 256;
+// partial sums that a block of 256 lanes leaves, one per wavefront (the split
+// half-sweep's blocks hold a wavefront's sites, so a sum does not depend on the kernel)
+constexpr int PARTS = 4;
 
 int hop_grid(long n);
 int blas_grid(long n);
@@ -140,11 +143,12 @@ int blas_grid(long n);
 // single-RHS launches and cached in batched ones.
 enum HopOrder { ORD_PLAIN = 0, ORD_ZSLAB = 1, ORD_TSLAB = 2 };
 constexpr int HOP_VARIANTS = 5;
+inline int hop_order(int v) { return v == 0 ? ORD_PLAIN : v <= 2 ? ORD_ZSLAB : ORD_TSLAB; }
 bool hop_variant_valid(const Geom &g, int v);
 // whether the (spinor precision, link format) pairing has every variant; the
 // others always run variant 0 whatever HopTune asks for
 bool hop_all_variants(int prec, int link_fmt);
-// blocks per RHS (= per-block partial sums written with a norm) of variant v;
+// blocks of HOP_BLOCK sites per RHS of variant v (PARTS partial sums each with a norm);
 // lanes_per_site = 2 for doublets in the general kernel (a lane pair per site)
 int hop_grid_variant(const Geom &g, int v, int lanes_per_site = 1);
 
@@ -155,6 +159,21 @@ inline int hop_phase_mask(const OpParams &op)
     for (int mu = 0; mu < 4; mu++)
         if (op.ph[mu][0] != 1.0 || op.ph[mu][1] != 0.0) m |= 1 << mu;
     return m;
+}
+// whether a single-field launch (not a doublet's) runs in the split kernel
+// (hop_split.h), in the block order of its variant (2 as 1, 4 as 3), without a
+// cap.  FP64 and FP32: always; it is the faster one from 4^4 (FP64 K1 4.3
+// against 7.1 us) to 32^3x64 (213 against 223 us).  16-bit: up to three
+// quarters of a 256-lane block per CU.  Below, the lanes of the 16-bit kernel
+// leave CUs idle (K1 6.0 us at 8^3x16 and 7.0 us at 20x10x14x18, split 4.0 and
+// 5.1 us); from one block per CU on its vector instructions bound it and the
+// split kernel executes more of them (6.7 against 7.1 us at 16^3x32, 57 against
+// 78 us at 32^3x64).
+inline bool hop_takes_split(const Geom &g, int prec, int link_fmt)
+{
+    if (prec == P64) return true;
+    if (prec == P32) return link_fmt == LK32R;
+    return link_fmt == LK16R && g.vh <= 49152;
 }
 // whether a launch of 16-bit spinors on FP16 two-row links runs in the 16-bit
 // kernel (hop16_kernel): 32-bit offsets (V/2 < 2^26) and a boundary phase in
@@ -169,8 +188,8 @@ inline int hop_nd_lanes(const Geom &g, int prec, int link_fmt, const OpParams &o
 
 // Hop half-sweep: out(h) over the V/2 sites of parity out_par for every RHS
 // of rl; `in` holds parity 1 - out_par; `self` (data may be nullptr unless
-// the epilogue needs it) holds parity out_par.  partial != nullptr: per-block
-// sums of |out|^2 at partial[r * pstride + block].  scal != nullptr: blocks of
+// the epilogue needs it) holds parity out_par.  partial != nullptr: sums of
+// |out|^2 per wavefront at partial[r * pstride + PARTS * block + wavefront].  scal != nullptr: blocks of
 // RHS r with scal[r].done set do nothing.
 // Launch shape of a hop half-sweep, chosen by the autotuner.
 struct HopTune {
@@ -185,8 +204,8 @@ hipError_t launch_hop(const Geom &g, int out_par, const FieldDesc &in, const Fie
                       const RhsList &rl, double *partial, long pstride, const CgScalars *scal, const HopTune &tu,
                       hipStream_t st, const CgFields *cg = nullptr);
 
-// Vector kernels over the n sites of each RHS of rl.  Reductions write
-// blas_grid(n) per-block sums at partial[r * pstride + block]; scalars come
+// Vector kernels over the n sites of each RHS of rl.  Reductions write the
+// wavefronts' sums of blas_grid(n) blocks at partial[r * pstride + PARTS * block + wavefront]; scalars come
 // from scal[r]; skip_done: blocks of RHS with scal[r].done do nothing.
 hipError_t launch_norm2(const FieldDesc &v, const RhsList &rl, double *partial, long pstride, hipStream_t st);
 hipError_t launch_convert(const FieldDesc &in, const FieldDesc &out, const RhsList &rl, hipStream_t st);
@@ -207,7 +226,7 @@ hipError_t launch_twist(const FieldDesc &in, const FieldDesc &out, const RhsList
 // x64 += xs ; xs = 0
 hipError_t launch_accumulate(const FieldDesc &x64, const FieldDesc &xs, const RhsList &rl, hipStream_t st);
 
-// Scalar kernels (one block per RHS): deterministic sums of nparts partials.
+// Scalar kernels (one block per RHS): deterministic sums of the partials of nparts blocks.
 enum ScalarOp {
     SC_INIT = 0,     // bb = rr = sum ; target = tol2 * (relative ? bb : 1) ; counters cleared
     SC_ALPHA = 1,    // pAp = sum ; alpha = rr / pAp
@@ -219,6 +238,8 @@ enum ScalarOp {
 hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long pstride, int nparts,
                          CgScalars *scal, double tol2, int relative, bool skip_done, CgScalars *publish,
                          hipStream_t st);
+// out[i] = sum of the partials of nparts blocks of RHS rl.idx[i], in the order of the scalar kernels
+hipError_t launch_sums(const RhsList &rl, const double *partial, long pstride, int nparts, double *out, hipStream_t st);
 // out[0] = deterministic maximum of partial[0..n)
 hipError_t launch_max(const double *partial, int n, double *out, hipStream_t st);
 // b = a, bytes / 16 lanes of 16 bytes (bandwidth calibration)

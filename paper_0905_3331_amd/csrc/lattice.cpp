@@ -180,7 +180,7 @@ int lattice_create(const int dims[4], int device, Lattice **out)
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
         L->lds_per_block = lds;
     // per RHS: at least as many partials as any hop variant or vector kernel writes
-    L->pstride = hop_grid(2 * L->g.vh) + 64;
+    L->pstride = PARTS * (hop_grid(2 * L->g.vh) + 64);
     for (auto &p : L->partial)
         if (hipMalloc((void **)&p, sizeof(double) * L->pstride * MAX_RHS) != hipSuccess)
             return fail(TMQ_ENOMEM, "partials");
@@ -379,8 +379,10 @@ static int tune_hop(Lattice *L, int key, int out_par, const FieldDesc &in, const
         return TMQ_OK;
     };
     const int nv = hop_all_variants(in.prec, lk.fmt) ? HOP_VARIANTS : 1;
+    const bool split = rl.n == 1 && hop_takes_split(L->g, in.prec, lk.fmt);
     for (int v = 0; v < nv; v++) {
         if (!hop_variant_valid(L->g, v)) continue;
+        if (split && (v == 2 || v == 4)) continue;  // the split kernel has the block orders only
         float us = 0.f;
         TMQ_TRY(time_one(v, 0, &us));
         L->hop_tune_us[key][v] = us;
@@ -390,10 +392,11 @@ static int tune_hop(Lattice *L, int key, int out_par, const FieldDesc &in, const
         }
     }
     // then a cap on the blocks per CU for the chosen variant (fewer sites in
-    // flight per XCD: a smaller working set in its L2)
+    // flight per XCD: a smaller working set in its L2); the split kernel holds
+    // a third of the sites in flight and takes none
     int occ = 0;
     L->hop_occ_us[key][0] = best_us;
-    for (int c = 1; c <= 5; c++) {
+    for (int c = 1; c <= 5 && !split; c++) {
         const unsigned lds = occ_lds(L, c);
         if (lds == ~0u) continue;
         float us = 0.f;

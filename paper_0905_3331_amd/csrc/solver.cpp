@@ -90,14 +90,18 @@ int solve_batch(Lattice *L, int n, const tmq_params *p, const tmq_solver_opts &o
     return status;
 }
 
-// the sum of nb per-block partials (device), on the host in a fixed order
+// the sum of the partials of nb blocks (device), on the host in a fixed order
 static int field_norm2_partials(Lattice *, const double *partial, int nb, hipStream_t st, double *out)
 {
-    std::vector<double> part(nb);
-    TMQ_HIP(hipMemcpyAsync(part.data(), partial, sizeof(double) * nb, hipMemcpyDeviceToHost, st));
+    std::vector<double> part((size_t)PARTS * nb);
+    TMQ_HIP(hipMemcpyAsync(part.data(), partial, sizeof(double) * part.size(), hipMemcpyDeviceToHost, st));
     TMQ_HIP(hipStreamSynchronize(st));
     double s = 0.0;
-    for (double x : part) s += x;
+    for (int k = 0; k < nb; k++) {
+        double b = 0.0;
+        for (int q = 0; q < PARTS; q++) b += part[(size_t)PARTS * k + q];
+        s += b;
+    }
     *out = s;
     return TMQ_OK;
 }
@@ -246,20 +250,15 @@ int solve_qhat_bicgstab(Lattice *L, const tmq_params &p, int sign, const tmq_sol
 // and psi_o = A^-1 Qhat^+ g5 phi'_o for sign -1, A = Qhat^+ Qhat^- by CG.
 // The residual phi - M psi is recomputed in FP64 on the full lattice; while
 // it is above the tolerance the same steps solve for the correction.
-// per-RHS |v|^2 of the RHS in rl of a batched FP64 field, summed on the host in a fixed order
+// per-RHS |v|^2 of the RHS in rl of a batched FP64 field (through L->partial[1])
 static int field_norms(Lattice *L, const FieldDesc &v, const RhsList &rl, hipStream_t st, std::vector<double> &out)
 {
-    const int nb = blas_grid(v.n);
     TMQ_HIP(launch_norm2(v, rl, L->partial[2], L->pstride, st));
-    std::vector<double> part((size_t)L->pstride * MAX_RHS);
-    TMQ_HIP(hipMemcpyAsync(part.data(), L->partial[2], sizeof(double) * part.size(), hipMemcpyDeviceToHost, st));
+    TMQ_HIP(launch_sums(rl, L->partial[2], L->pstride, blas_grid(v.n), L->partial[1], st));
+    std::vector<double> sums((size_t)rl.n);
+    TMQ_HIP(hipMemcpyAsync(sums.data(), L->partial[1], sizeof(double) * sums.size(), hipMemcpyDeviceToHost, st));
     TMQ_HIP(hipStreamSynchronize(st));
-    for (int i = 0; i < rl.n; i++) {
-        const int r = rl.idx[i];
-        double s = 0.0;
-        for (int k = 0; k < nb; k++) s += part[(size_t)r * L->pstride + k];
-        out[r] = s;
-    }
+    for (int i = 0; i < rl.n; i++) out[rl.idx[i]] = sums[(size_t)i];
     return TMQ_OK;
 }
 

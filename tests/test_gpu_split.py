@@ -1,0 +1,70 @@
+"""The split half-sweep (one field, the eight hops of a site in eight
+wavefronts of a 64-site block) against the FP64 oracle and against the batched
+kernel, at the sizes where its tiles, slabs and rules change.
+
+Tolerances are those of test_gpu_parity.py: the normwise bounds of the storage
+precision and the per-site bound derived there; a batch runs the lane-per-site
+kernel, whose numbers the split kernel has to give bit for bit.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from test_gpu_parity import SITE_BOUND, THETA, THETA_GEN, dev, host, rel, site_err, tmq  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# one partial tile; two whole ones; slabs of one and two planes (z, t) with
+# tiles that end inside a row; the last and the first 16-bit sizes of the rule
+EDGES = [(2, 2, 2, 2), (4, 4, 4, 4), (10, 10, 4, 6), (12, 18, 6, 14), (32, 16, 12, 16), (32, 16, 14, 16)]
+
+
+@pytest.mark.parametrize("theta", [THETA, THETA_GEN], ids=["t", "all"])
+@pytest.mark.parametrize("variant", [0, 1, 3])
+@pytest.mark.parametrize("dims", EDGES, ids=lambda d: "x".join(map(str, d)))
+def test_split_half_sweep(tmq, dims, variant, theta, monkeypatch):  # noqa: F811
+    monkeypatch.setenv("TMQ_HOP_VARIANT", str(variant))
+    U = synth.random_gauge(dims, seed=301)
+    lat = tmq.Lattice(dims)  # a lattice of its own: the forced variant is read at creation
+    lat.load_gauge(U)
+    psi = synth.gaussian_odd(dims, seed=31)
+    p = tmq.params(0.1632, 0.004, theta)
+    ref = oracle.Qhat(U, psi, 0.1632, 0.004, +1, theta)
+    for prec, tol in (("fp64", 1e-13), ("fp32", 2e-6), ("fp16", 3e-3), ("bf16", 2.5e-2)):
+        got = host(lat.apply_Qhat(p, +1, dev(psi), prec=prec))
+        assert rel(got, ref) < tol and site_err(got, ref) < SITE_BOUND[prec], (prec, rel(got, ref))
+    # every epilogue of a solve (norms, CG update, true residual), alone (split) and in a batch
+    bs = [dev(psi), dev(synth.gaussian_odd(dims, seed=32))]
+    ps = [p, tmq.params(0.16, 0.011, theta)]
+    for sloppy in ("fp64", "fp32", "fp16"):
+        opts = tmq.solver_opts(tol=1e-9, sloppy=sloppy, sloppy_link="fp32" if sloppy == "fp32" else "fp16")
+        xs, infos = lat.solve_batch(ps, bs, opts)
+        for i in range(2):
+            x, info = lat.solve(ps[i], bs[i], opts)
+            assert info.status == 0 and info.iters == infos[i].iters
+            assert torch.equal(x, xs[i]), (sloppy, i)
+    lat.close()
+
+
+@pytest.mark.parametrize("dims", EDGES[:4], ids=lambda d: "x".join(map(str, d)))
+def test_split_other_site_terms(tmq, dims):  # noqa: F811
+    """The epilogues of the full-lattice operator and of M^-1, and links that are not SU(3)."""
+    U = synth.random_gauge(dims, seed=302)
+    V = int(np.prod(dims))
+    lat = tmq.Lattice(dims)
+    psi = synth.gaussian_spinor(dims + (4, 3), seed=33)
+    p = tmq.params(0.15, 0.02, THETA_GEN)
+    for links in (U, 1.02 * U):
+        lat.load_gauge(links)
+        for sign in (+1, -1):
+            got = host(lat.apply_Q_full(p, sign, dev(psi.reshape(V, 4, 3))))
+            ref = oracle.Q(links, psi, 0.15, 0.02, sign, THETA_GEN).reshape(V, 4, 3)
+            assert rel(got, ref) < 1e-13 and site_err(got, ref) < SITE_BOUND["fp64"]
+    lat.load_gauge(U)
+    x, info = lat.solve_M(p, +1, dev(psi.reshape(V, 4, 3)), tmq.solver_opts(tol=1e-10))
+    back = oracle.M(U, host(x).reshape(dims + (4, 3)), 0.15, 0.02, +1, THETA_GEN)
+    assert info.status == 0 and rel(back, psi) < 2e-10
+    lat.close()
