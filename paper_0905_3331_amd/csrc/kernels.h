@@ -276,13 +276,19 @@ hipError_t launch_bi_xr(const FieldDesc &x, const FieldDesc &p, const FieldDesc 
 hipError_t launch_bi_scalar(int op, const double *p0, const double *p1, const double *p2, int nparts,
                             BicgScalars *s, double tol2, int relative, BicgScalars *publish, hipStream_t st);
 
-// the whole full-lattice FP64 CG on Q^+ Q^- of a tiny lattice in one
-// workgroup (small_cg.hip): f = {b, x, r, p, t, ap}, stacked full fields;
-// continues from x and the counters in *sc (zeroed before the first call),
-// ends with the true residual in sc->rr and sc->done set if it met the target
+// the whole full-lattice FP64 CG on Q^+ Q^- of a tiny lattice in one launch
+// (small_cg.hip): f = {b, x, r, p, t, p'}, stacked full fields; continues from
+// x and the counters in *sc (zeroed before the first call), ends with the true
+// residual in sc->rr and sc->done set if it met the target.  sync: device
+// memory of SMALL_SYNC_WORDS words for the blocks' exchanges; a block waits at
+// most `spin` wall-clock ticks for the others (they wait for a place on the
+// device while other launches fill it), then all give up: sc->pad is 1 and the
+// solve has to be done another way.
 constexpr long SMALL_CG_MAX_SITES = 1024;
+constexpr int SMALL_SYNC_WORDS = 64;
 hipError_t launch_small_cg(const Geom &g, const FieldDesc *f, const LinkDesc &lk, const OpParams &op, double tol2,
-                           int relative, int max_iter, CgScalars *sc, hipStream_t st);
+                           int relative, int max_iter, CgScalars *sc, unsigned long long *sync, long long spin,
+                           hipStream_t st);
 
 // a 4x4 complex spin matrix (row-major)
 struct SpinMat {

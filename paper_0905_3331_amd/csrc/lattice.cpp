@@ -179,6 +179,7 @@ int lattice_create(const int dims[4], int device, Lattice **out)
         L->lds_per_cu = lds;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
         L->lds_per_block = lds;
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeWallClockRate, device) == hipSuccess && lds > 0) L->wall_khz = lds;
     // per RHS: at least as many partials as any hop variant or vector kernel writes
     L->pstride = PARTS * (hop_grid(2 * L->g.vh) + 64);
     for (auto &p : L->partial)

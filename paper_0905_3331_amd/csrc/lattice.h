@@ -104,6 +104,7 @@ struct Lattice {
     // blocks-per-CU cap tuned for that variant (0: none; see launch_hop's lds)
     int hop_occ[NKEY];
     float hop_occ_us[NKEY][6];
+    int wall_khz = 100000;  // rate of the device's wall clock
     int lds_per_cu = 65536;
     int lds_per_block = 65536;  // largest LDS reservation of one block
     // autotuned launch shape of batched hops, per (spinor precision, link

@@ -410,7 +410,7 @@ static int read_scalars(Lattice *L, int n, hipStream_t st, std::vector<CgScalars
 
 // Small lattices are launch-latency bound (a 4^4 iteration is nine kernels
 // of a few microseconds).  Tiny ones (at most SMALL_CG_MAX_SITES sites) run
-// the whole CG in one workgroup (small_cg.hip); on the others up to
+// the whole CG in one launch (small_cg.hip); on the others up to
 // GRAPH_MAX_SITES sites the iterations run as HIP graphs of CHUNK
 // iterations each, captured once per solve, two graphs publishing their
 // scalars to the two halves of the ring so that the host reads one chunk
@@ -437,33 +437,40 @@ int solve_full(Lattice *L, const tmq_params &p, const tmq_solver_opts &o, const 
     const double tol2 = o.tol * o.tol;
     const long ps = L->pstride;
     if (n <= SMALL_CG_MAX_SITES && !L->timing && !getenv("TMQ_NO_SMALL_CG")) {
-        // the whole CG in one workgroup (small_cg.hip); called again from its
-        // true residual if that has not met the target
+        // the whole CG in one launch (small_cg.hip); called again from its true
+        // residual if that has not met the target, and left for the plain
+        // launches below if its blocks did not get onto the device together
+        // (TMQ_SMALL_CG_SPIN: the ticks a block waits for the others)
         const FieldDesc f[6] = {b, x, r, pp, t, ap};
         TMQ_HIP(launch_zero(x, one, st));
         TMQ_HIP(hipMemsetAsync(S, 0, sizeof(CgScalars), st));
         std::vector<CgScalars> cur;
+        const char *es = getenv("TMQ_SMALL_CG_SPIN");
+        const long long spin = es ? atoll(es) : (long long)L->wall_khz * 200;  // 0.2 s
         for (int call = 0;; call++) {
-            TMQ_HIP(launch_small_cg(L->g, f, lk, op, tol2, o.relative, max_iter, S, st));
+            TMQ_HIP(launch_small_cg(L->g, f, lk, op, tol2, o.relative, max_iter, S,
+                                    (unsigned long long *)L->partial[0], spin, st));
             TMQ_TRY(read_scalars(L, 1, st, cur));
-            if (cur[0].done || cur[0].nan || cur[0].iter >= max_iter || call >= 20) break;
+            if (cur[0].done || cur[0].nan || cur[0].iter >= max_iter || call >= 20 || cur[0].pad) break;
         }
-        int status = TMQ_OK;
-        if (cur[0].nan) {
-            status = TMQ_ENAN;
-            set_error("tmq_solve_full: non-finite value in CG");
-        } else if (!cur[0].done) {
-            status = TMQ_ENOCONV;
-            set_error("tmq_solve_full: max_iter reached before the tolerance");
+        if (!cur[0].pad) {
+            int status = TMQ_OK;
+            if (cur[0].nan) {
+                status = TMQ_ENAN;
+                set_error("tmq_solve_full: non-finite value in CG");
+            } else if (!cur[0].done) {
+                status = TMQ_ENOCONV;
+                set_error("tmq_solve_full: max_iter reached before the tolerance");
+            }
+            if (info) {
+                info->status = status;
+                info->iters = cur[0].iter;
+                info->reliable_updates = cur[0].reliable;
+                info->true_rel_residual = cur[0].bb > 0 ? std::sqrt(cur[0].rr / cur[0].bb) : std::sqrt(cur[0].rr);
+                info->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+            }
+            return status;
         }
-        if (info) {
-            info->status = status;
-            info->iters = cur[0].iter;
-            info->reliable_updates = cur[0].reliable;
-            info->true_rel_residual = cur[0].bb > 0 ? std::sqrt(cur[0].rr / cur[0].bb) : std::sqrt(cur[0].rr);
-            info->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-        }
-        return status;
     }
     const bool graphs = n <= GRAPH_MAX_SITES && !L->timing && !getenv("TMQ_NO_GRAPH");
     if (graphs) {

@@ -68,3 +68,67 @@ def test_split_other_site_terms(tmq, dims):  # noqa: F811
     back = oracle.M(U, host(x).reshape(dims + (4, 3)), 0.15, 0.02, +1, THETA_GEN)
     assert info.status == 0 and rel(back, psi) < 2e-10
     lat.close()
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 8), (2, 10, 4, 6), (8, 4, 4, 8)], ids=lambda d: "x".join(map(str, d)))
+def test_small_full_cg(tmq, dims, monkeypatch):  # noqa: F811
+    """The one-launch CG of tiny lattices over several blocks (two parities in
+    one tile, a partial last tile, the largest size), and the way back to plain
+    launches when its blocks give up waiting for each other (bounded wait of no
+    ticks: every block leaves at once)."""
+    V = int(np.prod(dims))
+    U = synth.random_gauge(dims, seed=303)
+    lat = tmq.Lattice(dims)
+    lat.load_gauge(U)
+    b = synth.gaussian_spinor(dims + (4, 3), seed=34).reshape(-1, 4, 3)
+    p = tmq.params(0.16, 0.01, THETA_GEN)
+    for opts in (tmq.solver_opts(tol=1e-10), tmq.solver_opts(tol=1e-13)):
+        x, info = lat.solve_full(p, dev(b), opts)
+        res = oracle.true_residual(U, b, host(x), 0.16, 0.01, THETA_GEN, eo=False)
+        assert info.status == 0 and res <= opts.tol and abs(res - info.true_rel_residual) <= 1e-2 * res
+        monkeypatch.setenv("TMQ_SMALL_CG_SPIN", "-1")
+        x2, info2 = lat.solve_full(p, dev(b), opts)
+        monkeypatch.delenv("TMQ_SMALL_CG_SPIN")
+        assert info2.status == 0 and abs(info2.iters - info.iters) <= 2
+        assert oracle.true_residual(U, b, host(x2), 0.16, 0.01, THETA_GEN, eo=False) <= opts.tol
+    lat.close()
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (10, 10, 4, 6), (32, 16, 8, 16), (32, 16, 8, 18)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_canonical_buffers_in_place(tmq, dims):  # noqa: F811
+    """Half-sweeps that read and write the caller's buffers: sizes on both sides
+    of the rule (32 K sites), the operators in place, and the reduced
+    precisions' results equal to the values their storage holds."""
+    V = int(np.prod(dims))
+    U = synth.random_gauge(dims, seed=304)
+    lat = tmq.Lattice(dims)
+    lat.load_gauge(U)
+    p = tmq.params(0.1632, 0.004, THETA)
+    psi = dev(synth.gaussian_odd(dims, seed=35))
+    full = dev(synth.gaussian_spinor(dims + (4, 3), seed=36).reshape(V, 4, 3))
+    for prec in ("fp64", "fp32", "fp16", "bf16"):
+        out = lat.apply_Qhat(p, -1, psi, prec=prec)
+        ref = oracle.Qhat(U, host(psi), 0.1632, 0.004, -1, THETA)
+        assert rel(host(out), ref) < {"fp64": 1e-13, "fp32": 2e-6, "fp16": 3e-3, "bf16": 2.5e-2}[prec]
+        v = psi.clone()
+        lat.apply_Qhat(p, -1, v, out=v, prec=prec)
+        assert torch.equal(v, out), prec
+        if prec in ("fp16", "bf16"):
+            codes, scale = lat.encode(out, prec)  # stored values encode to themselves
+            dt = torch.float16 if prec == "fp16" else torch.bfloat16
+            back = codes.view(dt).float() * scale[:, None]
+            assert torch.equal(back.double(), torch.view_as_real(out).reshape(-1, 24))
+        elif prec == "fp32":
+            assert torch.equal(torch.view_as_real(out).float().double(), torch.view_as_real(out))
+    out = lat.apply_QhatQhat(p, psi)
+    assert rel(host(out), oracle.QhatQhat(U, host(psi), 0.1632, 0.004, THETA)) < 1e-13
+    v = psi.clone()
+    lat.apply_QhatQhat(p, v, out=v)
+    assert torch.equal(v, out)
+    out = lat.apply_Q_full(p, +1, full)
+    assert rel(host(out), oracle.Q(U, host(full).reshape(dims + (4, 3)), 0.1632, 0.004, +1, THETA).reshape(V, 4, 3)) < 1e-13
+    v = full.clone()
+    lat.apply_Q_full(p, +1, v, out=v)
+    assert torch.equal(v, out)
+    lat.close()
