@@ -72,19 +72,38 @@ int check_ptrs(const void *a, const void *b)
     return TMQ_OK;
 }
 
+bool overlap(const double *a, const double *b, size_t bytes)
+{
+    return (const char *)a < (const char *)b + bytes && (const char *)b < (const char *)a + bytes;
+}
+
+// Makes fi and fo the caller's canonical buffers where the half-sweeps of Qhat
+// can read and write them; true if that is both of them.  Overlapping buffers
+// keep the conversion of the input.
+bool qhat_in_place(const Lattice *L, const OpParams &op, int prec, const LinkDesc &lk, const double *in, double *out,
+                   FieldDesc *fi, FieldDesc *fo)
+{
+    const long vh = L->g.vh;
+    const bool ci = hop_reads_canonical(L->g, prec, lk.fmt, vh) && !overlap(in, out, (size_t)vh * 12 * 16);
+    const bool co = hop_writes_canonical(L->g, prec, lk.fmt, op);
+    if (ci) *fi = canonical_desc(prec, in, vh, LAY_CANONICAL);
+    if (co) *fo = canonical_desc(prec, out, vh, LAY_CANONICAL);
+    return ci && co;
+}
+
 // odd-site Qhat on device canonical buffers
 int qhat_dev(Lattice *L, const tmq_params *p, int sign, int prec, const double *in, double *out, hipStream_t st)
 {
     const long vh = L->g.vh;
     FieldDesc fi, fo, te;
-    TMQ_TRY(work_field(L, "op_in", prec, vh, &fi));
-    TMQ_TRY(work_field(L, "op_out", prec, vh, &fo));
-    TMQ_TRY(work_field(L, "op_te", prec, vh, &te));
     const LinkDesc lk = lattice_links(L, link_fmt_for(L, prec, prec == TMQ_FP32 ? P32 : P16));
-    TMQ_HIP(launch_from_canonical((const double2 *)in, fi, st));
-    TMQ_TRY(apply_Qhat(L, make_op(L, p, 1), sign, fi, fo, te, lk, rhs_all(1), nullptr, nullptr, st));
-    TMQ_HIP(launch_to_canonical(fo, (double2 *)out, st));
-    return TMQ_OK;
+    const OpParams op = make_op(L, p, 1);
+    if (!qhat_in_place(L, op, prec, lk, in, out, &fi, &fo)) {
+        if (!fi.layout) TMQ_TRY(work_field(L, "op_in", prec, vh, &fi));
+        if (!fo.layout) TMQ_TRY(work_field(L, "op_out", prec, vh, &fo));
+    }
+    TMQ_TRY(work_field(L, "op_te", prec, vh, &te));
+    return apply_Qhat_canonical(L, op, sign, (const double2 *)in, (double2 *)out, fi, fo, te, lk, st);
 }
 
 int check_nd(const tmq_nd_params *p)
@@ -241,8 +260,8 @@ int tmq_apply_Qhat_noalloc_dev(tmq_lattice *lat, const tmq_params *p, int sign, 
     // the three work fields of qhat_dev, one after the other in the array
     const long vh = L->g.vh;
     size_t b0 = 0, b1 = 0, b2 = 0;
-    const FieldDesc fi = field_at(base, prec, vh, &b0);
-    const FieldDesc fo = field_at(base + b0, prec, vh, &b1);
+    FieldDesc fi = field_at(base, prec, vh, &b0);
+    FieldDesc fo = field_at(base + b0, prec, vh, &b1);
     const FieldDesc te = field_at(base + b0 + b1, prec, vh, &b2);
     if (b0 + b1 + b2 > cap) {
         char msg[256];
@@ -260,10 +279,9 @@ int tmq_apply_Qhat_noalloc_dev(tmq_lattice *lat, const tmq_params *p, int sign, 
         ~NoAllocScope() { L->no_alloc = false; }
     } scope{L};
     L->no_alloc = true;
-    TMQ_HIP(launch_from_canonical((const double2 *)in, fi, st));
-    TMQ_TRY(apply_Qhat(L, make_op(L, p, 1), sign, fi, fo, te, lk, rhs_all(1), nullptr, nullptr, st));
-    TMQ_HIP(launch_to_canonical(fo, (double2 *)out, st));
-    return TMQ_OK;
+    const OpParams op = make_op(L, p, 1);
+    qhat_in_place(L, op, prec, lk, in, out, &fi, &fo);
+    return apply_Qhat_canonical(L, op, sign, (const double2 *)in, (double2 *)out, fi, fo, te, lk, st);
 }
 
 int tmq_apply_Qhat(tmq_lattice *lat, const tmq_params *p, int sign, tmq_prec prec, const double *in, double *out)
@@ -296,16 +314,19 @@ int tmq_apply_QhatQhat_dev(tmq_lattice *lat, const tmq_params *p, const double *
     DeviceGuard dg(L->device);
     hipStream_t st = (hipStream_t)stream;
     const long vh = L->g.vh;
-    FieldDesc fi, fo, te, to;
-    TMQ_TRY(work_field(L, "op_in", P64, vh, &fi));
-    TMQ_TRY(work_field(L, "op_out", P64, vh, &fo));
+    FieldDesc fi, te, to;
+    const LinkDesc lk = lattice_links(L, link_fmt_for(L, P64, P64));
     TMQ_TRY(work_field(L, "op_te", P64, vh, &te));
     TMQ_TRY(work_field(L, "op_to", P64, vh, &to));
-    TMQ_HIP(launch_from_canonical((const double2 *)in, fi, st));
-    TMQ_TRY(apply_QhatQhat(L, make_op(L, p, 1), fi, fo, te, to, lattice_links(L, link_fmt_for(L, P64, P64)),
-                           rhs_all(1), nullptr, nullptr, st));
-    TMQ_HIP(launch_to_canonical(fo, (double2 *)out, st));
-    return TMQ_OK;
+    // (the input is read for the last time before the output is written)
+    if (hop_reads_canonical(L->g, P64, lk.fmt, vh)) {
+        fi = canonical_desc(P64, in, vh, LAY_CANONICAL);
+    } else {
+        TMQ_TRY(work_field(L, "op_in", P64, vh, &fi));
+        TMQ_HIP(launch_from_canonical((const double2 *)in, fi, st));
+    }
+    return apply_QhatQhat(L, make_op(L, p, 1), fi, canonical_desc(P64, out, vh, LAY_CANONICAL), te, to, lk, rhs_all(1),
+                          nullptr, nullptr, st);
 }
 
 int tmq_apply_Q_full_dev(tmq_lattice *lat, const tmq_params *p, int sign, const double *in, double *out,
@@ -319,14 +340,16 @@ int tmq_apply_Q_full_dev(tmq_lattice *lat, const tmq_params *p, int sign, const 
     DeviceGuard dg(L->device);
     hipStream_t st = (hipStream_t)stream;
     const long n = 2 * L->g.vh;
-    FieldDesc fi, fo;
-    TMQ_TRY(work_field(L, "full_in", P64, n, &fi));
-    TMQ_TRY(work_field(L, "full_out", P64, n, &fo));
-    TMQ_HIP(launch_full_from_canonical(L->g, (const double2 *)in, fi, st));
-    TMQ_TRY(apply_Q_full(L, make_op(L, p, 1), sign, fi, fo, lattice_links(L, link_fmt_for(L, P64, P64)),
-                         rhs_all(1), st));
-    TMQ_HIP(launch_full_to_canonical(L->g, fo, (double2 *)out, st));
-    return TMQ_OK;
+    const OpParams op = make_op(L, p, 1);
+    const LinkDesc lk = lattice_links(L, link_fmt_for(L, P64, P64));
+    // (if the buffers overlap, the second half-sweep would read what the first has written)
+    FieldDesc fi = canonical_desc(P64, in, n, LAY_CANONICAL_FULL);
+    const FieldDesc fo = canonical_desc(P64, out, n, LAY_CANONICAL_FULL);
+    if (!hop_reads_canonical(L->g, P64, lk.fmt, n) || overlap(in, out, (size_t)n * 12 * 16)) {
+        TMQ_TRY(work_field(L, "full_in", P64, n, &fi));
+        TMQ_HIP(launch_full_from_canonical(L->g, (const double2 *)in, fi, st));
+    }
+    return apply_Q_full(L, op, sign, fi, fo, lk, rhs_all(1), st);
 }
 
 int tmq_apply_Q_full(tmq_lattice *lat, const tmq_params *p, int sign, const double *in, double *out)

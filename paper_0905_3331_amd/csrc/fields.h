@@ -303,6 +303,29 @@ struct Sp16 {
             st<NT>(q + k * 8, make_uint4(w[0], w[1], w[2], w[3]));
         }
     }
+    // the FP32 values of a site as store() and load() would give them, to a
+    // canonical complex128 site
+    template <typename R>
+    static __device__ __forceinline__ void store_decoded(double2 *q, const spinor<R> &s)
+    {
+        float m = 0.f;
+        bool bad = false;
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            const float a = fabsf((float)s.c[k / 3][k % 3].re), b = fabsf((float)s.c[k / 3][k % 3].im);
+            bad |= !(a <= 3.0e38f) || !(b <= 3.0e38f);
+            m = fmaxf(m, fmaxf(a, b));
+        }
+        const bool tiny = m < 1.17549435e-38f;
+        const float inv = tiny ? 0.f : 1.0f / m;
+        const float sc = bad ? __int_as_float(0x7fc00000) : (tiny ? 0.f : m);
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            const cx<R> v = s.c[k / 3][k % 3];
+            q[k] = make_double2((double)(code_to_f32<BF>(f32_to_code<BF>((float)v.re * inv)) * sc),
+                                (double)(code_to_f32<BF>(f32_to_code<BF>((float)v.im * inv)) * sc));
+        }
+    }
 };
 using SpH16 = Sp16<false>;
 using SpB16 = Sp16<true>;

@@ -45,7 +45,8 @@ struct XsOf<SpF64> {
     using type = SpF64;
 };
 
-enum HopEp { EP_STORE = 0, EP_CG = 1, EP_RES = 2 };
+// (EP_CAN: EP_STORE to a canonical complex128 buffer)
+enum HopEp { EP_STORE = 0, EP_CG = 1, EP_RES = 2, EP_CAN = 3 };
 
 // Divisors of a batched 16-bit launch's block and site decode (FastDiv): the
 // blocks of an RHS group per XCD (grp), the group size (gsz) and the size of
@@ -104,6 +105,7 @@ struct HopArgs {
     // fused epilogues (EPI_K2_CG, EPI_K2_RES)
     BatchView<SP> cg_r, cg_p;
     BatchView<typename XsOf<SP>::type> cg_x;
+    double2 *can_out;  // EP_CAN: the canonical output
     // batched 16-bit launches
     SiteDiv dv;
     EpiCoef ec[MAX_RHS];
@@ -517,6 +519,9 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs<SP, LK> &a, const s
 #pragma unroll
             for (int c = 0; c < 3; c++) o.c[i][c] = bb.c[i][c] - o.c[i][c];
         a.cg_r.at(rhs).store(h, o);
+    } else if (EP == EP_CAN) {
+        // the site as it would be stored and read back
+        if constexpr (SP::coded) SP::store_decoded(a.can_out + 12 * h, o);
     } else {
         a.out.at(rhs).template store<NTOUT>(h, o);
     }
@@ -1279,7 +1284,12 @@ void go16_e(const HopArgs<SP, L16R> &a, bool s, bool n, int ep, dim3 grid, dim3 
     else if (ep == EP_RES)
         hipLaunchKernelGGL((hop16_kernel<SP, true, true, ORD, SB, EP_RES, ND, PM, false, BATCH, TWO>), grid, block, lds,
                            st, a);
-    else if (s && !ND && a.epi == EPI_K2) {
+    else if (ep == EP_CAN) {
+        // (a single field's K2, no norm)
+        if constexpr (!ND && !BATCH)
+            hipLaunchKernelGGL((hop16_kernel<SP, true, false, ORD, SB, EP_CAN, ND, PM, true, BATCH, TWO>), grid, block,
+                               lds, st, a);
+    } else if (s && !ND && a.epi == EPI_K2) {
         if (n)
             hipLaunchKernelGGL((hop16_kernel<SP, true, true, ORD, SB, EP_STORE, ND, PM, true, BATCH, TWO>), grid, block,
                                lds, st, a);
@@ -1417,7 +1427,7 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
               long pstride, const CgScalars *scal, const HopTune &tu, hipStream_t st, const CgFields *cg)
 {
     if (rl.n <= 0) return hipSuccess;
-    const int ep = epi == EPI_K2_CG ? EP_CG : epi == EPI_K2_RES ? EP_RES : EP_STORE;
+    int ep = epi == EPI_K2_CG ? EP_CG : epi == EPI_K2_RES ? EP_RES : EP_STORE;
     if (ep != EP_STORE) {
         // fused epilogues: the vectors must be given, in the right formats, the
         // norm asked for, and (for CG) the device scalars holding alpha
@@ -1435,6 +1445,7 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
     a.in = make_bv<SP>(in);
     a.self = self.data ? make_bv<SP>(self) : a.in;
     a.out = make_bv<SP>(out);
+    a.can_out = (double2 *)out.data;
     a.lk = make_lk<LK>(lk);
     a.op = op;
     a.rl = rl;
@@ -1442,7 +1453,7 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
     a.pstride = pstride;
     a.scal = scal;
     a.one = 1.0f;
-    if (ep != EP_STORE) {
+    if (ep == EP_CG || ep == EP_RES) {
         a.cg_r = make_bv<SP>(cg->r);
         a.cg_p = make_bv<SP>(cg->p);
         if (ep == EP_CG) a.cg_x = make_bv<typename XsOf<SP>::type>(cg->x);
@@ -1456,6 +1467,14 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
             return launch_split<SP, LK>(g, out_par, in, self, out, lk, op, epi, sign, rl, partial, pstride, scal,
                                         hop_order(variant), hop_grid_variant(g, variant), st, cg);
         }
+    }
+    // (other launches: the 16-bit kernel alone writes a canonical output, of K2)
+    if (in.layout || self.layout) return hipErrorInvalidValue;
+    if (ep == EP_STORE && out.layout) {
+        if (out.layout != LAY_CANONICAL || epi != EPI_K2 || partial || rl.n != 1 || rl.idx[0] != 0 || op.nd ||
+            !SP::coded || !__is_same(LK, L16R) || !hop16_ok(g, hop_phase_mask(op)))
+            return hipErrorInvalidValue;
+        ep = EP_CAN;
     }
     // the divisors and site-term table of a batched 16-bit launch of ntup tuples
     auto batch16 = [&](int ntup) {
@@ -1530,7 +1549,7 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
     dim3 grid(a.nblk * ntup), block(HOP_BLOCK);
     const bool s = epi != EPI_K1, n = partial != nullptr;
     if (s && !self.data) return hipErrorInvalidValue;
-    a.epi = ep == EP_STORE ? epi : EPI_K2;
+    a.epi = ep == EP_STORE || ep == EP_CAN ? epi : EPI_K2;
     const bool nt = rl.n == 1;
     const unsigned lds = tu.lds;
     if (!ALL) {

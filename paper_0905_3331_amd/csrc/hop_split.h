@@ -34,6 +34,10 @@ namespace tmq {
 constexpr int SPLIT_SITES = 64;    // sites per block
 constexpr int SPLIT_THREADS = 512;  // eight wavefronts
 
+// which operands are canonical complex128 buffers: the input, the own-site
+// field, the output; and whether these hold the whole lattice
+enum SplitCan { CAN_IN = 1, CAN_SELF = 2, CAN_OUT = 4, CAN_FULL = 8 };
+
 template <class SP, class LK>
 struct SplitArgs {
     using R = typename LK::real;
@@ -50,6 +54,8 @@ struct SplitArgs {
     float one;  // 1.0, opaque to the compiler (see code_lo in fields.h)
     SP cg_r, cg_p;
     typename XsOf<SP>::type cg_x;
+    const double2 *cin, *cself;  // canonical operands (SplitCan)
+    double2 *cout;
     SiteDiv dv;
     // site-term coefficients, formed on the host in FP64 by the operations of
     // hop_epilogue and rounded once: K1 {c, c m}, K2 {m}, FULL {m, kappa}, SRC
@@ -83,6 +89,11 @@ struct SplitIo<SpF64> {
     static constexpr int UC = 2, NU = 6;
     using Raw = spinor<double>;
     static __device__ __forceinline__ void load(const SpF64 &f, long h, Raw &r) { f.load(h, r); }
+    static __device__ __forceinline__ void to_canonical(double2 *q, const cx<R> (&v)[UC], float)
+    {
+        q[0] = make_double2(v[0].re, v[0].im);
+        q[1] = make_double2(v[1].re, v[1].im);
+    }
     static __device__ __forceinline__ void load_unit(const SpF64 &f, long h, int u, cx<R> (&v)[UC])
     {
         const double2 *q = f.p + aidx(h, 2 * u, 12);
@@ -104,6 +115,11 @@ struct SplitIo<SpF32> {
     static constexpr int UC = 2, NU = 6;
     using Raw = spinor<float>;
     static __device__ __forceinline__ void load(const SpF32 &f, long h, Raw &r) { f.load(h, r); }
+    static __device__ __forceinline__ void to_canonical(double2 *q, const cx<R> (&v)[UC], float)
+    {
+        q[0] = make_double2((double)v[0].re, (double)v[0].im);
+        q[1] = make_double2((double)v[1].re, (double)v[1].im);
+    }
     static __device__ __forceinline__ void load_unit(const SpF32 &f, long h, int u, cx<R> (&v)[UC])
     {
         const float4 a = f.p[aidx(h, u, 6)];
@@ -144,6 +160,16 @@ struct SplitIo<Sp16<BF>> {
         for (int k = 0; k < 4; k++) w[k] = pack16(f32_to_code<BF>(v[k].re * inv), f32_to_code<BF>(v[k].im * inv));
         f.p[aidx(h, u, 3)] = make_uint4(w[0], w[1], w[2], w[3]);
         if (u == 0) f.scale[h] = bad ? __int_as_float(0x7fc00000) : (tiny ? 0.f : m);
+    }
+    // the same piece as it would be read back, to a canonical buffer
+    static __device__ __forceinline__ void to_canonical(double2 *q, const cx<R> (&v)[UC], float m)
+    {
+        const bool bad = !(m <= 3.0e38f), tiny = m < 1.17549435e-38f;
+        const float inv = tiny ? 0.f : 1.0f / m, sc = bad ? __int_as_float(0x7fc00000) : (tiny ? 0.f : m);
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            q[k] = make_double2((double)(code_to_f32<BF>(f32_to_code<BF>(v[k].re * inv)) * sc),
+                                (double)(code_to_f32<BF>(f32_to_code<BF>(v[k].im * inv)) * sc));
     }
 };
 
@@ -243,9 +269,15 @@ __device__ __forceinline__ void split_sum(const R2 (*sh)[6][SPLIT_SITES], const 
 
 // the block's place on the lattice, the same for its eight wavefronts
 struct SplitSite {
-    uint32_t t, z, y, xh, h, pidx;
+    uint32_t t, z, y, xh, x, h, pidx;
     bool active;  // the lane has a site
     int lane;
+    // index in a canonical buffer of one parity, or (FULL) of the whole lattice
+    template <bool FULL>
+    __device__ __forceinline__ uint32_t site() const
+    {
+        return FULL ? 2 * (h - xh) + x : h;
+    }
 };
 
 // LDS of a block
@@ -258,7 +290,7 @@ struct SplitShared {
 };
 
 // wavefront W's work
-template <int W, class SP, class LK, bool SELF, bool NORM, int EP>
+template <int W, class SP, class LK, bool SELF, bool NORM, int EP, int CAN>
 __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShared<SP> &S, const SplitSite &p)
 {
     using IO = SplitIo<SP>;
@@ -278,12 +310,12 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
     using RX = typename XS::real;
     cx<RX> xx[UC];
     if (p.active) {
-        // the wavefront's neighbour and link
-        uint32_t hn;
+        // the wavefront's neighbour (eo index hn; x coordinate xn) and link
+        uint32_t hn, xn = p.x;
         const uint32_t XH = (uint32_t)g.XH, plane = (uint32_t)g.LY * XH;
         if constexpr (MU == 1) {
-            const uint32_t x = 2 * p.xh + ((a.out_par + p.t + p.z + p.y) & 1), LX = (uint32_t)g.LX;
-            const uint32_t xn = BACK ? (x == 0 ? LX - 1 : x - 1) : (x + 1 == LX ? 0u : x + 1);
+            const uint32_t LX = (uint32_t)g.LX;
+            xn = BACK ? (p.x == 0 ? LX - 1 : p.x - 1) : (p.x + 1 == LX ? 0u : p.x + 1);
             hn = h - p.xh + (xn >> 1);
         } else {
             const uint32_t c = MU == 0 ? p.t : MU == 2 ? p.y : p.z;
@@ -294,9 +326,28 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
         typename LK::Loaded u;
         typename IO::Raw raw;
         a.lk.template load_link<true>(BACK ? a.out_par ^ 1 : a.out_par, MU, BACK ? hn : h, u);
-        IO::load(a.in, hn, raw);
+        if constexpr (CAN & CAN_IN) {
+            // the conversion to the device format is this rounding
+            const double2 *q = a.cin + 12L * ((CAN & CAN_FULL) ? 2 * (hn - (xn >> 1)) + xn : hn);
+#pragma unroll
+            for (int c = 0; c < 12; c++) {
+                const double2 v = q[c];
+                raw.c[c / 3][c % 3] = cx<R>{(R)v.x, (R)v.y};
+            }
+        } else {
+            IO::load(a.in, hn, raw);
+        }
         if constexpr (UNIT) {
-            if (SELF) IO::load_unit(a.self, h, W, sf);
+            if constexpr ((CAN & CAN_SELF) && SELF) {
+                const double2 *q = a.cself + 12L * p.site<(CAN & CAN_FULL) != 0>() + W * UC;
+#pragma unroll
+                for (int n = 0; n < UC; n++) {
+                    const double2 v = q[n];
+                    sf[n] = cx<R>{(R)v.x, (R)v.y};
+                }
+            } else if (SELF) {
+                IO::load_unit(a.self, h, W, sf);
+            }
             if (EP == EP_CG) {
                 IO::load_unit(a.cg_r, h, W, rr);
                 IO::load_unit(a.cg_p, h, W, pp);
@@ -379,6 +430,8 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
             if constexpr (EP == EP_CG) store_x<UC>(a.cg_x, h, W, xx);
             if constexpr (SP::coded)
                 S.shm[W][lane] = m;
+            else if constexpr (CAN & CAN_OUT)
+                IO::to_canonical(a.cout + 12L * p.site<(CAN & CAN_FULL) != 0>() + W * UC, o, 0.f);
             else
                 IO::store_unit(EP == EP_STORE ? a.out : a.cg_r, h, W, o);
         }
@@ -392,9 +445,13 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
                 if constexpr (NORM)
 #pragma unroll
                     for (int n = 0; n < UC; n++) shn[(W * UC + n) * SPLIT_SITES + lane] = n2[n];
-                if constexpr (SP::coded)
-                    IO::store_unit(EP == EP_STORE ? a.out : a.cg_r, h, W, o,
-                                   fmaxf(S.shm[0][lane], fmaxf(S.shm[1][lane], S.shm[2][lane])));
+                if constexpr (SP::coded) {
+                    const float mx = fmaxf(S.shm[0][lane], fmaxf(S.shm[1][lane], S.shm[2][lane]));
+                    if constexpr (CAN & CAN_OUT)
+                        IO::to_canonical(a.cout + 12L * h + W * UC, o, mx);
+                    else
+                        IO::store_unit(EP == EP_STORE ? a.out : a.cg_r, h, W, o, mx);
+                }
             }
         }
         if constexpr (NORM) {
@@ -414,7 +471,7 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
     }
 }
 
-template <class SP, class LK, bool SELF, bool NORM, int EP>
+template <class SP, class LK, bool SELF, bool NORM, int EP, int CAN = 0>
 __global__ __launch_bounds__(SPLIT_THREADS) void hop_split_kernel(SplitArgs<SP, LK> a)
 {
     if (a.scal && a.scal[a.rhs].done) return;
@@ -458,16 +515,17 @@ __global__ __launch_bounds__(SPLIT_THREADS) void hop_split_kernel(SplitArgs<SP, 
         p.pidx = PARTS * (8 * (sb / PARTS) + j) + sb % PARTS;
     }
     p.h = ((p.t * LZ + p.z) * LY + p.y) * XH + p.xh;
+    p.x = 2 * p.xh + ((a.out_par + p.t + p.z + p.y) & 1);  // (t + z + y + x) = out_par mod 2
     // (the eight roles run through the same barriers)
     switch (w) {
-    case 0: split_role<0, SP, LK, SELF, NORM, EP>(a, S, p); break;
-    case 1: split_role<1, SP, LK, SELF, NORM, EP>(a, S, p); break;
-    case 2: split_role<2, SP, LK, SELF, NORM, EP>(a, S, p); break;
-    case 3: split_role<3, SP, LK, SELF, NORM, EP>(a, S, p); break;
-    case 4: split_role<4, SP, LK, SELF, NORM, EP>(a, S, p); break;
-    case 5: split_role<5, SP, LK, SELF, NORM, EP>(a, S, p); break;
-    case 6: split_role<6, SP, LK, SELF, NORM, EP>(a, S, p); break;
-    default: split_role<7, SP, LK, SELF, NORM, EP>(a, S, p); break;
+    case 0: split_role<0, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
+    case 1: split_role<1, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
+    case 2: split_role<2, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
+    case 3: split_role<3, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
+    case 4: split_role<4, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
+    case 5: split_role<5, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
+    case 6: split_role<6, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
+    default: split_role<7, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
     }
 }
 
@@ -482,7 +540,7 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
     static_assert(SPLIT_SITES * PARTS == HOP_BLOCK, "a tile is the sites of one partial sum");
     const int ep = epi == EPI_K2_CG ? EP_CG : epi == EPI_K2_RES ? EP_RES : EP_STORE;
     const int r = rl.idx[0];
-    auto field = [&](const FieldDesc &f) { return make_sp<SP>(f.data ? field_rhs(f, r) : f); };
+    auto field = [&](const FieldDesc &f) { return make_sp<SP>(f.data && !f.layout ? field_rhs(f, r) : f); };
     SplitArgs<SP, LK> a;
     a.g = g;
     a.out_par = out_par;
@@ -504,6 +562,15 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
         a.cg_p = field(cg->p);
         if (ep == EP_CG) a.cg_x = make_sp<typename XsOf<SP>::type>(field_rhs(cg->x, r));
     }
+    // canonical operands: the input with the own-site field (if any), the output
+    const bool fused = ep != EP_STORE, sl = self.data != nullptr;
+    const int full = in.layout == LAY_CANONICAL_FULL || out.layout == LAY_CANONICAL_FULL ? CAN_FULL : 0;
+    const int can = (in.layout ? CAN_IN : 0) | (sl && self.layout ? CAN_SELF : 0) |
+                    (!fused && out.layout ? CAN_OUT : 0) | full;
+    if (can && (fused || partial || r != 0)) return hipErrorInvalidValue;
+    a.cin = (const double2 *)in.data;
+    a.cself = (const double2 *)self.data;
+    a.cout = (double2 *)out.data;
     a.dv = make_site_div(g, ord, nblk, 1, 1);
     const double kap = op.kappa[r], m = sign * op.mut[r];
     double e[4] = {m, kap, 0.0, 0.0};
@@ -519,6 +586,25 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
     for (int q = 0; q < 4; q++) a.co[q] = (R)e[q];
     const dim3 grid(nblk * PARTS), block(SPLIT_THREADS);
     const bool s = a.epi != EPI_K1, n = partial != nullptr;
+    if (can) {
+#define SPLIT_CAN(SELF, CAN)                                                                              \
+    if (s == SELF && can == (CAN)) {                                                                      \
+        hipLaunchKernelGGL((hop_split_kernel<SP, LK, SELF, false, EP_STORE, CAN>), grid, block, 0, st, a); \
+        return hipGetLastError();                                                                         \
+    }
+        SPLIT_CAN(true, CAN_OUT)
+        if constexpr (!SP::coded) {
+            SPLIT_CAN(false, CAN_IN)
+            SPLIT_CAN(true, CAN_SELF | CAN_OUT)
+        }
+        if constexpr (__is_same(SP, SpF64)) {
+            SPLIT_CAN(true, CAN_SELF)
+            SPLIT_CAN(true, CAN_OUT | CAN_FULL)
+            SPLIT_CAN(true, CAN_IN | CAN_SELF | CAN_OUT | CAN_FULL)
+        }
+#undef SPLIT_CAN
+        return hipErrorInvalidValue;
+    }
     if (ep == EP_CG)
         hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, true, EP_CG>), grid, block, 0, st, a);
     else if (ep == EP_RES)

@@ -34,12 +34,19 @@ struct Geom {
     long vh;  // V / 2
 };
 
+// How a field is laid out: the device layout of its precision, or a caller's
+// canonical complex128 buffer that a half-sweep reads or writes itself
+// (rounded to the precision on the way: the numbers are those of a conversion
+// pass), [V/2][12] of one parity or [V][12] of the whole lattice.
+enum Layout { LAY_DEVICE = 0, LAY_CANONICAL = 1, LAY_CANONICAL_FULL = 2 };
+
 // A batch of spinor fields, each of n sites (one parity, or both parities
 // stacked: even sites 0..V/2-1, odd sites V/2..V-1) in the 8-site chunked
 // layout of fields.h; RHS r starts rhs_elems elements (and rhs_sites scales)
 // after RHS 0.
 struct FieldDesc {
     int prec = P64;
+    int layout = LAY_DEVICE;
     void *data = nullptr;   // element type by prec: double2, float4, uint4
     float *scale = nullptr; // FP32 per-site scale of 16-bit formats
     long n = 0;             // sites per RHS (a multiple of 8)
@@ -48,6 +55,16 @@ struct FieldDesc {
     long rhs_sites = 0;
 };
 
+// a canonical buffer as the input or output of a half-sweep in precision prec
+inline FieldDesc canonical_desc(int prec, const void *buf, long n, int layout)
+{
+    FieldDesc d;
+    d.prec = prec;
+    d.layout = layout;
+    d.data = (void *)buf;
+    d.n = n;
+    return d;
+}
 // sub-view starting at site `off` (a multiple of 8), n sites, every RHS
 FieldDesc field_sub(const FieldDesc &f, long off, long n);
 // the single field of RHS r
@@ -184,6 +201,25 @@ inline bool hop16_ok(const Geom &g, int phase_mask) { return g.vh < (1L << 26) &
 inline int hop_nd_lanes(const Geom &g, int prec, int link_fmt, const OpParams &op)
 {
     return (prec == P16 || prec == PB16) && link_fmt == LK16R && hop16_ok(g, hop_phase_mask(op)) ? 1 : 2;
+}
+
+// Which single-field half-sweeps take canonical buffers (Layout).  Output (no
+// norm, no fused update): the split kernel and the 16-bit kernel, at any size:
+// it saves the conversion pass (Qhat at 32^3x64: FP64 614 -> 560 us, FP32 352
+// -> 325, FP16 250 -> 236; at 8^3x16 19.2 -> 16.1).  Input: the split kernel in
+// FP64 and FP32 (a 16-bit site would be encoded eight times), of buffers of at
+// most 32 K sites (6 MB): a launch less (Qhat FP64 8^3x16 16.1 -> 13.2 us,
+// 20x10x14x18 25.1 -> 22.1); above, its 192-byte strides, read eight times
+// over, cost more than the pass (16^3x32 41.5 -> 42.0, FP32 at 32^3x64 325 ->
+// 410, the full operator 768 -> 944).
+inline bool hop_reads_canonical(const Geom &g, int prec, int link_fmt, long sites)
+{
+    return (prec == P64 || prec == P32) && hop_takes_split(g, prec, link_fmt) && sites <= 32768;
+}
+inline bool hop_writes_canonical(const Geom &g, int prec, int link_fmt, const OpParams &op)
+{
+    return hop_takes_split(g, prec, link_fmt) ||
+           ((prec == P16 || prec == PB16) && link_fmt == LK16R && hop16_ok(g, hop_phase_mask(op)));
 }
 
 // Hop half-sweep: out(h) over the V/2 sites of parity out_par for every RHS

@@ -558,6 +558,13 @@ static FieldDesc flavour_view(const FieldDesc &f)
     return o;
 }
 
+// what a canonical buffer moves beyond the field of its precision
+static double canonical_extra_bytes(const FieldDesc &in, const FieldDesc &self, const FieldDesc &out)
+{
+    const double sp = in.prec == P64 ? 192.0 : in.prec == P32 ? 96.0 : 52.0;
+    return (192.0 - sp) * ((in.layout != 0) + (self.data && self.layout != 0) + (out.data && out.layout != 0));
+}
+
 static double fused_extra_bytes(int prec, int epi)
 {
     // the epilogue's own vectors beside the half-sweep's (whose output write
@@ -704,7 +711,8 @@ int hop(Lattice *L, int out_par, const FieldDesc &in, const FieldDesc &self, con
     if (L->timing) {
         t.a = pool_event(L);
         t.b = pool_event(L);
-        t.bytes = (hop_bytes_per_site(in.prec, lk.fmt, epi != EPI_K1, rl.n) + fused_extra_bytes(in.prec, epi) * rl.n) *
+        t.bytes = (hop_bytes_per_site(in.prec, lk.fmt, epi != EPI_K1, rl.n) + fused_extra_bytes(in.prec, epi) * rl.n +
+                   canonical_extra_bytes(in, self, out)) *
                   (double)L->g.vh;
         t.flops = 1320.0 * (double)L->g.vh * rl.n;
         t.prec = in.prec;
@@ -764,12 +772,24 @@ int apply_QhatQhat(Lattice *L, const OpParams &op, const FieldDesc &in, const Fi
     return TMQ_OK;
 }
 
+int apply_Qhat_canonical(Lattice *L, const OpParams &op, int sign, const double2 *in, double2 *out,
+                         const FieldDesc &fi, const FieldDesc &fo, const FieldDesc &te, const LinkDesc &lk,
+                         hipStream_t st)
+{
+    if (!fi.layout) TMQ_HIP(launch_from_canonical(in, fi, st));
+    TMQ_TRY(apply_Qhat(L, op, sign, fi, fo, te, lk, rhs_all(1), nullptr, nullptr, st));
+    if (!fo.layout) TMQ_HIP(launch_to_canonical(fo, out, st));
+    return TMQ_OK;
+}
+
 int apply_Q_full(Lattice *L, const OpParams &op, int sign, const FieldDesc &in, const FieldDesc &out,
                  const LinkDesc &lk, const RhsList &rl, hipStream_t st)
 {
     const long vh = L->g.vh;
-    const FieldDesc ie = field_sub(in, 0, vh), io = field_sub(in, vh, vh);
-    const FieldDesc oe = field_sub(out, 0, vh), oo = field_sub(out, vh, vh);
+    // (a canonical full field is given whole to both half-sweeps)
+    auto part = [&](const FieldDesc &f, long off) { return f.layout ? f : field_sub(f, off, vh); };
+    const FieldDesc ie = part(in, 0), io = part(in, vh);
+    const FieldDesc oe = part(out, 0), oo = part(out, vh);
     TMQ_TRY(hop(L, 0, io, ie, oe, lk, op, EPI_FULL, sign, rl, nullptr, nullptr, st));
     TMQ_TRY(hop(L, 1, ie, io, oo, lk, op, EPI_FULL, sign, rl, nullptr, nullptr, st));
     return TMQ_OK;

@@ -154,6 +154,12 @@ int hop(Lattice *L, int out_par, const FieldDesc &in, const FieldDesc &self, con
         const CgScalars *scal, hipStream_t st, const CgFields *cg = nullptr);
 
 // Qhat^{sign} in -> out (odd fields), tmp_e an even work field; partial: |out|^2 per block
+// out = Qhat in on canonical odd-site buffers: fi and fo describe them as
+// canonical where the half-sweeps read and write them in place, and are work
+// fields for conversion passes where not
+int apply_Qhat_canonical(Lattice *L, const OpParams &op, int sign, const double2 *in, double2 *out,
+                         const FieldDesc &fi, const FieldDesc &fo, const FieldDesc &te, const LinkDesc &lk,
+                         hipStream_t st);
 int apply_Qhat(Lattice *L, const OpParams &op, int sign, const FieldDesc &in, const FieldDesc &out,
                const FieldDesc &tmp_e, const LinkDesc &lk, const RhsList &rl, double *partial,
                const CgScalars *scal, hipStream_t st);
