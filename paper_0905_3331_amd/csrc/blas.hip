@@ -149,28 +149,55 @@ __global__ __launch_bounds__(BLAS_BLOCK) void k_twist(BatchView<SpF64> in, Batch
     }
 }
 
-// p = r + beta p
-template <class F>
-__global__ __launch_bounds__(BLAS_BLOCK) void k_xpay(BatchView<F> r, BatchView<F> p, long n, RhsList rl,
-                                                     const CgScalars *sc, int skip_done)
+// x += alpha p where pending, then p = r + beta p.  The update of x was in
+// the half-sweep that forms r, which read p for it a second time; here p is at
+// hand (a CG iteration moves one field less: FP16 52, FP64 192 bytes per site).
+template <class FX, class F>
+__global__ __launch_bounds__(BLAS_BLOCK) void k_xpay(BatchView<F> r, BatchView<F> p, BatchView<FX> x, long n,
+                                                     RhsList rl, const CgScalars *sc, int skip_done, int has_x,
+                                                     int only_x)
 {
     using R = typename F::real;
+    using RX = typename FX::real;
     BLOCK_RHS(rl);
-    if (skip_done && sc[rhs].done) return;
-    const R b = (R)sc[rhs].beta;
+    const bool up_x = has_x && sc[rhs].xpend, up_p = !only_x && !(skip_done && sc[rhs].done);
+    if (!up_x && !up_p) return;
     const long h = (long)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if (h < n) {
         spinor<R> rs, ps;
-        r.at(rhs).load(h, rs);
         p.at(rhs).load(h, ps);
+        if (up_p) r.at(rhs).load(h, rs);
+        if (up_x) {
+            const RX a = (RX)sc[rhs].alpha;
+            spinor<RX> xs;
+            if (sc[rhs].fresh) {
 #pragma unroll
-        for (int i = 0; i < 4; i++)
+                for (int i = 0; i < 4; i++)
 #pragma unroll
-            for (int j = 0; j < 3; j++) {
-                ps.c[i][j].re = fmad(b, ps.c[i][j].re, rs.c[i][j].re);
-                ps.c[i][j].im = fmad(b, ps.c[i][j].im, rs.c[i][j].im);
+                    for (int j = 0; j < 3; j++) xs.c[i][j] = cx<RX>{RX(0), RX(0)};
+            } else {
+                x.at(rhs).load(h, xs);
             }
-        p.at(rhs).store(h, ps);
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    xs.c[i][j].re = fmad(a, (RX)ps.c[i][j].re, xs.c[i][j].re);
+                    xs.c[i][j].im = fmad(a, (RX)ps.c[i][j].im, xs.c[i][j].im);
+                }
+            x.at(rhs).store(h, xs);
+        }
+        if (up_p) {
+            const R b = (R)sc[rhs].beta;
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    ps.c[i][j].re = fmad(b, ps.c[i][j].re, rs.c[i][j].re);
+                    ps.c[i][j].im = fmad(b, ps.c[i][j].im, rs.c[i][j].im);
+                }
+            p.at(rhs).store(h, ps);
+        }
     }
 }
 
@@ -195,29 +222,99 @@ __global__ __launch_bounds__(BLAS_BLOCK) void k_residual(BatchView<SpF64> b, Bat
     WRITE_PARTIAL(partial, pstride, part)
 }
 
-template <class FS>
-__global__ __launch_bounds__(BLAS_BLOCK) void k_accumulate(BatchView<SpF64> x, BatchView<FS> xs, long n,
-                                                           RhsList rl)
+// x += xs, xs completed by its pending alpha p on the way (not stored: it is
+// fresh after this).  What counts as zero is not read.
+template <class F>
+__global__ __launch_bounds__(BLAS_BLOCK) void k_accumulate(BatchView<SpF64> x, BatchView<SpF32> xs, BatchView<F> p,
+                                                           long n, RhsList rl, const CgScalars *sc)
 {
-    using RS = typename FS::real;
     BLOCK_RHS(rl);
     const long h = (long)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if (h < n) {
         spinor<double> a;
-        spinor<RS> d, z;
-        x.at(rhs).load(h, a);
-        xs.at(rhs).load(h, d);
+        spinor<float> d, ps;
+        if (sc[rhs].reliable) {
+            x.at(rhs).load(h, a);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) a.c[i][j] = cx<double>{0.0, 0.0};
+        }
+        if (sc[rhs].fresh) {
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) d.c[i][j] = cx<float>{0.f, 0.f};
+        } else {
+            xs.at(rhs).load(h, d);
+        }
+        if (sc[rhs].xpend) {
+            const float al = (float)sc[rhs].alpha;
+            p.at(rhs).load(h, ps);
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    d.c[i][j].re = fmad(al, ps.c[i][j].re, d.c[i][j].re);
+                    d.c[i][j].im = fmad(al, ps.c[i][j].im, d.c[i][j].im);
+                }
+        }
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
             for (int j = 0; j < 3; j++) {
                 a.c[i][j].re += (double)d.c[i][j].re;
                 a.c[i][j].im += (double)d.c[i][j].im;
-                z.c[i][j] = cx<RS>{RS(0), RS(0)};
             }
         x.at(rhs).store(h, a);
-        xs.at(rhs).store(h, z);
     }
+}
+
+__global__ __launch_bounds__(BLAS_BLOCK) void k_add(BatchView<SpF64> x, BatchView<SpF64> d, long n, RhsList rl)
+{
+    BLOCK_RHS(rl);
+    const long h = (long)blockIdx.x * BLAS_BLOCK + threadIdx.x;
+    if (h < n) {
+        spinor<double> a, b;
+        x.at(rhs).load(h, a);
+        d.at(rhs).load(h, b);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int j = 0; j < 3; j++) a.c[i][j] = a.c[i][j] + b.c[i][j];
+        x.at(rhs).store(h, a);
+    }
+}
+
+// b, r and p of a new right-hand side from its canonical source, with |b|^2:
+// one pass instead of a conversion, three copies and a norm of their own
+template <class F>
+__global__ __launch_bounds__(BLAS_BLOCK) void k_join(const double2 *src, SpF64 b, F r, F p, long n, double *partial)
+{
+    constexpr int rhs = 0;
+    const long h = (long)blockIdx.x * BLAS_BLOCK + threadIdx.x;
+    double part = 0.0;
+    if (h < n) {
+        spinor<double> s;
+        const double2 *q = src + h * 12;
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            const double2 v = q[k];
+            s.c[k / 3][k % 3] = cx<double>{v.x, v.y};
+        }
+        b.store(h, s);
+        r.store(h, s);
+        if constexpr (F::coded) {  // p is a copy of the stored r
+            spinor<float> t;
+            r.load(h, t);
+            p.store(h, t);
+        } else {
+            p.store(h, s);
+        }
+        part = site_norm2(s);
+    }
+    WRITE_PARTIAL(partial, 0, part)
 }
 
 // ------------------------------------------------------------- scalars
@@ -230,11 +327,20 @@ __device__ __forceinline__ double det_sum(const double *partial, int n, double *
 {
     static_assert(PARTS == 4, "a block's partial sums are two 16-byte words");
     double v = 0.0;
-    for (int i = threadIdx.x; i < n; i += SC_THREADS) {
-        const double2 a = ((const double2 *)partial)[2 * i], b = ((const double2 *)partial)[2 * i + 1];
-        v += (((0.0 + a.x) + a.y) + b.x) + b.y;
+    constexpr int U = 4;  // loads asked for together
+    for (int i = threadIdx.x; i < n; i += U * SC_THREADS) {
+        double2 a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int k = min(i + u * SC_THREADS, n - 1);
+            a[u] = ((const double2 *)partial)[2 * k];
+            b[u] = ((const double2 *)partial)[2 * k + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (i + u * SC_THREADS < n) v += (((0.0 + a[u].x) + a[u].y) + b[u].x) + b[u].y;
     }
-    return block_sum(v, sh);  // valid in thread 0
+    return block_sum_n<SC_THREADS / 64>(v, sh);  // valid in thread 0
 }
 
 __device__ __forceinline__ int finite(double v) { return isfinite(v) ? 1 : 0; }
@@ -242,12 +348,20 @@ __device__ __forceinline__ int finite(double v) { return isfinite(v) ? 1 : 0; }
 // one block per RHS of rl (grid x)
 __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const double *partial, long pstride,
                                                        int nparts, CgScalars *sc, double tol2, int relative,
-                                                       int skip_done, CgScalars *publish)
+                                                       int skip_done, int defer, CgScalars *publish)
 {
     const int rhs = rl.idx[blockIdx.x];
-    CgScalars *s = sc + rhs;
+    // (the scalars are read ahead of the sum and written back whole)
+    CgScalars c = sc[rhs], *s = &c;
+    if (op == SC_BETA && s->xpend) {
+        s->fresh = 0;
+        s->xpend = 0;
+    }
     if (skip_done && s->done) {
-        if (publish && threadIdx.x == 0) publish[rhs] = *s;
+        if (threadIdx.x == 0) {
+            sc[rhs] = c;
+            if (publish) publish[rhs] = c;
+        }
         return;
     }
     __shared__ double sh[SC_THREADS / 64];
@@ -261,6 +375,8 @@ __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const
         s->alpha = s->beta = s->pAp = 0.0;
         s->iter = 0;
         s->reliable = 0;
+        s->xpend = 0;
+        s->fresh = defer;
         s->last_true = 1;
         s->nan = !finite(sum);
         s->done = (sum < s->target || sum == 0.0 || s->nan) ? 1 : 0;
@@ -276,6 +392,7 @@ __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const
         s->beta = sum / s->rr_prev;
         s->iter += 1;
         s->last_true = 0;
+        s->xpend = defer;
         if (!finite(sum) || !finite(s->beta)) s->nan = 1;
         s->done = (sum < s->target || s->nan) ? 1 : 0;
         break;
@@ -284,11 +401,14 @@ __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const
         s->beta = s->rr_prev > 0.0 ? sum / s->rr_prev : 0.0;
         s->reliable += 1;
         s->last_true = 1;
+        s->xpend = 0;
+        s->fresh = defer;
         if (!finite(sum)) s->nan = 1;
         s->done = (sum < s->target || sum == 0.0 || s->nan) ? 1 : 0;
         break;
     }
-    if (publish) publish[rhs] = *s;
+    sc[rhs] = c;
+    if (publish) publish[rhs] = c;
 }
 
 // out[i] = the sum of RHS rl.idx[i]
@@ -378,12 +498,19 @@ hipError_t launch_axpy_norm(const FieldDesc &x, const FieldDesc &p, const FieldD
     return hipGetLastError();
 }
 
-hipError_t launch_xpay(const FieldDesc &r, const FieldDesc &p, const RhsList &rl, const CgScalars *s,
-                       bool skip_done, hipStream_t st)
+hipError_t launch_xpay(const FieldDesc &r, const FieldDesc &p, const FieldDesc &x, const RhsList &rl,
+                       const CgScalars *s, bool skip_done, bool only_x, hipStream_t st)
 {
-    if (r.prec != p.prec) return hipErrorInvalidValue;
+    const int hx = x.data ? 1 : 0, sk = skip_done ? 1 : 0, ox = only_x ? 1 : 0;
+    if (r.prec != p.prec || (hx && x.prec != (p.prec == P64 ? P64 : P32))) return hipErrorInvalidValue;
+    if (p.prec == P64) {
+        LAUNCH((k_xpay<SpF64, SpF64>), p.n, rl, st, make_bv<SpF64>(r), make_bv<SpF64>(p), make_bv<SpF64>(x), p.n, rl,
+               s, sk, hx, ox);
+        return hipGetLastError();
+    }
     DISPATCH_SP(p.prec, F,
-                LAUNCH(k_xpay<F>, p.n, rl, st, make_bv<F>(r), make_bv<F>(p), p.n, rl, s, skip_done ? 1 : 0));
+                LAUNCH((k_xpay<SpF32, F>), p.n, rl, st, make_bv<F>(r), make_bv<F>(p), make_bv<SpF32>(x), p.n, rl, s, sk,
+                       hx, ox));
     return hipGetLastError();
 }
 
@@ -396,21 +523,40 @@ hipError_t launch_residual(const FieldDesc &b, const FieldDesc &ax, const FieldD
     return hipGetLastError();
 }
 
-hipError_t launch_accumulate(const FieldDesc &x64, const FieldDesc &xs, const RhsList &rl, hipStream_t st)
+hipError_t launch_accumulate(const FieldDesc &x64, const FieldDesc &xs, const FieldDesc &p, const RhsList &rl,
+                             const CgScalars *s, hipStream_t st)
 {
-    if (x64.prec != P64) return hipErrorInvalidValue;
-    DISPATCH_SP(xs.prec, F,
-                LAUNCH(k_accumulate<F>, x64.n, rl, st, make_bv<SpF64>(x64), make_bv<F>(xs), x64.n, rl));
+    if (x64.prec != P64 || xs.prec != P32 || p.prec == P64) return hipErrorInvalidValue;
+    DISPATCH_SP(p.prec, F,
+                LAUNCH(k_accumulate<F>, x64.n, rl, st, make_bv<SpF64>(x64), make_bv<SpF32>(xs), make_bv<F>(p), x64.n,
+                       rl, s));
+    return hipGetLastError();
+}
+
+hipError_t launch_add(const FieldDesc &x, const FieldDesc &d, const RhsList &rl, hipStream_t st)
+{
+    if (x.prec != P64 || d.prec != P64 || x.n != d.n) return hipErrorInvalidValue;
+    LAUNCH(k_add, x.n, rl, st, make_bv<SpF64>(x), make_bv<SpF64>(d), x.n, rl);
+    return hipGetLastError();
+}
+
+hipError_t launch_join(const double2 *src, const FieldDesc &b, const FieldDesc &r, const FieldDesc &p, double *partial,
+                       hipStream_t st)
+{
+    if (b.prec != P64 || r.prec != p.prec || r.n != b.n || p.n != b.n) return hipErrorInvalidValue;
+    DISPATCH_SP(r.prec, F,
+                hipLaunchKernelGGL(k_join<F>, dim3(blas_grid(b.n)), dim3(BLAS_BLOCK), 0, st, src, make_sp<SpF64>(b),
+                                   make_sp<F>(r), make_sp<F>(p), b.n, partial));
     return hipGetLastError();
 }
 
 hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long pstride, int nparts,
-                         CgScalars *s, double tol2, int relative, bool skip_done, CgScalars *publish,
-                         hipStream_t st)
+                         CgScalars *s, double tol2, int relative, bool skip_done, bool defer,
+                         CgScalars *publish, hipStream_t st)
 {
     if (rl.n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_scalar, dim3(rl.n), dim3(SC_THREADS), 0, st, op, rl, partial, pstride, nparts, s, tol2,
-                       relative, skip_done ? 1 : 0, publish);
+                       relative, skip_done ? 1 : 0, defer ? 1 : 0, publish);
     return hipGetLastError();
 }
 

@@ -19,6 +19,25 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
     return s;
 }
 
+// block_sum of N wavefronts, the sums of the wavefronts read together
+template <int N>
+__device__ __forceinline__ double block_sum_n(double v, double *sh)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x == 0) {
+        double w[N];
+#pragma unroll
+        for (int i = 0; i < N; i++) w[i] = sh[i];
+#pragma unroll
+        for (int i = 0; i < N; i++) s += w[i];
+    }
+    return s;
+}
+
 // Sum over a wavefront, valid in every lane; block_sum adds these of a block
 // in the order of its wavefronts
 __device__ __forceinline__ double wave_sum(double v)

@@ -212,20 +212,15 @@ int engine_join(Engine *E, int slot, const tmq_params &p, const tmq_solver_opts 
     s.max_iter = o.max_iter > 0 ? o.max_iter : 10000;
     s.delta = o.delta > 0.0 && o.delta < 1.0 ? o.delta : engine_default_delta(E->sloppy, E->sloppy_link);
 
-    // x = 0 ; r = b ; p = r ; bb = |b|^2
+    // x = 0 ; r = b ; p = r ; bb = |b|^2 (x, and in mixed precision x_s, count
+    // as zero until they are written first; switch mode updates x in place)
     const RhsList one = list_of({slot});
     hipStream_t st = E->st;
-    TMQ_HIP(launch_from_canonical(b, field_rhs(E->b, slot), st));
-    TMQ_HIP(launch_zero(E->x, one, st));
-    TMQ_HIP(launch_convert(E->b, E->r64, one, st));
-    TMQ_HIP(launch_norm2(E->r64, one, E->partial[1], L->pstride, st));
+    double *part = E->partial[1] + slot * L->pstride;
+    TMQ_HIP(launch_join(b, field_rhs(E->b, slot), field_rhs(E->rs, slot), field_rhs(E->ps, slot), part, st));
+    if (E->switching) TMQ_HIP(launch_zero(E->x, one, st));
     TMQ_HIP(launch_scalar(SC_INIT, one, E->partial[1], L->pstride, blas_grid(E->n), E->scal, o.tol * o.tol,
-                          o.relative, false, nullptr, st));
-    if (E->mixed) {
-        TMQ_HIP(launch_convert(E->r64, E->rs, one, st));
-        TMQ_HIP(launch_zero(E->xs, one, st));
-    }
-    TMQ_HIP(launch_convert(E->rs, E->ps, one, st));
+                          o.relative, false, !E->switching, nullptr, st));
     s.state = Engine::RUNNING;
     s.joined_step = E->step_no;
     return TMQ_OK;
@@ -252,11 +247,12 @@ static int body_switched(Engine *E, const RhsList &al, CgScalars *pub)
     CgScalars *S = E->scal;
     TMQ_HIP(launch_convert(E->ps, E->pss, al, st));
     TMQ_TRY(apply_Qhat(L, E->op, -1, E->pss, E->tos, E->tes, E->lks, al, E->partial[0], S, st));
-    TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, L->hop_blocks_last, S, 0, 0, true, nullptr, st));
+    TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, L->hop_blocks_last, S, 0, 0, true, false, nullptr,
+                          st));
     TMQ_TRY(apply_Qhat(L, E->op, +1, E->tos, E->apss, E->tes, E->lks, al, nullptr, S, st));
     TMQ_HIP(launch_convert(E->apss, E->ap64, al, st));
     TMQ_HIP(launch_axpy_norm(E->x, E->ps, E->r64, E->ap64, al, S, E->partial[1], L->pstride, true, st));
-    TMQ_HIP(launch_scalar(SC_BETA, al, E->partial[1], L->pstride, blas_grid(E->n), S, 0, 0, true, pub, st));
+    TMQ_HIP(launch_scalar(SC_BETA, al, E->partial[1], L->pstride, blas_grid(E->n), S, 0, 0, true, false, pub, st));
     return TMQ_OK;
 }
 
@@ -280,26 +276,25 @@ static int enqueue_body(Engine *E, const std::vector<int> &all, const std::vecto
     if (al.n > 0 && E->switching) {
         // switch mode, slots still on the FP64 operator
         TMQ_TRY(apply_Qhat(L, E->op, -1, E->ps, E->to64, E->te64, E->lk64, al, E->partial[0], S, st));
-        TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, L->hop_blocks_last, S, 0, 0, true, nullptr,
-                              st));
+        TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, L->hop_blocks_last, S, 0, 0, true, false,
+                              nullptr, st));
         CgFields cg;
         cg.r = E->r64;
-        cg.p = E->ps;
-        cg.x = E->x;
         TMQ_TRY(apply_Qhat_cg(L, E->op, E->to64, E->te64, E->lk64, al, cg, E->partial[1], S, st));
-        TMQ_HIP(launch_scalar(SC_BETA, al, E->partial[1], L->pstride, L->hop_blocks_last, S, 0, 0, true, pub, st));
+        TMQ_HIP(launch_scalar(SC_BETA, al, E->partial[1], L->pstride, L->hop_blocks_last, S, 0, 0, true, true, pub,
+                              st));
     } else if (al.n > 0) {
         // t = Qhat^- p, <p, A p> = |t|^2 ; A p = Qhat^+ t
         TMQ_TRY(apply_Qhat(L, E->op, -1, E->ps, E->tos, E->tes, E->lks, al, E->partial[0], S, st));
-        TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, L->hop_blocks_last, S, 0, 0, true, nullptr,
-                              st));
-        // A p = Qhat^+ t fused with x_s += alpha p ; r -= alpha A p ; |r|^2 ; then beta
+        TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, L->hop_blocks_last, S, 0, 0, true, false,
+                              nullptr, st));
+        // A p = Qhat^+ t fused with r -= alpha A p ; |r|^2 ; then beta (x_s += alpha p
+        // goes with the update of p)
         CgFields cg;
         cg.r = E->rs;
-        cg.p = E->ps;
-        cg.x = E->xs;
         TMQ_TRY(apply_Qhat_cg(L, E->op, E->tos, E->tes, E->lks, al, cg, E->partial[1], S, st));
-        TMQ_HIP(launch_scalar(SC_BETA, al, E->partial[1], L->pstride, L->hop_blocks_last, S, 0, 0, true, pub, st));
+        TMQ_HIP(launch_scalar(SC_BETA, al, E->partial[1], L->pstride, L->hop_blocks_last, S, 0, 0, true, true, pub,
+                              st));
     }
     return TMQ_OK;
 }
@@ -378,17 +373,20 @@ bool engine_ready(Engine *E)
     return hipEventQuery(E->step_ev[(E->step_no - 1) % Lattice::RING]) == hipSuccess;
 }
 
-// x += x_s ; r = b - A x (FP64) ; the slot's scalars continue from |r|^2
+// x += x_s ; r = b - A x (FP64, stored in the inner format) ; the slot's
+// scalars continue from |r|^2
 static int reliable_update(Engine *E, const RhsList &rl, CgScalars *publish)
 {
     if (rl.n == 0) return TMQ_OK;
     Lattice *L = E->L;
     hipStream_t st = E->st;
-    if (E->mixed) TMQ_HIP(launch_accumulate(E->x, E->xs, rl, st));
-    TMQ_TRY(residual_QhatQhat(L, E->op, E->x, E->b, E->r64, E->te64, E->to64, E->lk64, rl, E->partial[2], st));
+    if (E->mixed)
+        TMQ_HIP(launch_accumulate(E->x, E->xs, E->ps, rl, E->scal, st));
+    else  // the update of x that this step's body left pending
+        TMQ_HIP(launch_xpay(E->rs, E->ps, E->x, rl, E->scal, true, true, st));
+    TMQ_TRY(residual_QhatQhat(L, E->op, E->x, E->b, E->rs, E->te64, E->to64, E->lk64, rl, E->partial[2], st));
     TMQ_HIP(launch_scalar(SC_RELIABLE, rl, E->partial[2], L->pstride, L->hop_blocks_last, E->scal, 0.0, 0, false,
-                          publish, st));
-    if (E->mixed) TMQ_HIP(launch_convert(E->r64, E->rs, rl, st));
+                          E->mixed, publish, st));
     return TMQ_OK;
 }
 
@@ -442,7 +440,7 @@ int engine_end_step(Engine *E, std::vector<int> *finished)
     }
     // reliable updates after this step's body publish to the same ring entry
     TMQ_TRY(reliable_update(E, list_of(ru), pub));
-    if (!in_body.empty()) TMQ_HIP(launch_xpay(E->rs, E->ps, list_of(in_body), E->scal, true, E->st));
+    if (!in_body.empty()) TMQ_HIP(launch_xpay(E->rs, E->ps, E->xs, list_of(in_body), E->scal, true, false, E->st));
     TMQ_HIP(hipEventRecord(E->step_ev[cur], E->st));
     E->step_no++;
     E->body_pending = false;
@@ -456,6 +454,9 @@ int engine_take(Engine *E, int slot, double2 *x, tmq_solve_info *info)
         return TMQ_ESTATE;
     }
     Engine::Slot &sl = E->slots[slot];
+    // a solve that ended before x was written first leaves x = 0
+    if (x && !E->switching && (E->mixed ? sl.last.reliable == 0 : sl.last.iter == 0))
+        TMQ_HIP(launch_zero(E->x, list_of({slot}), E->st));
     if (x) TMQ_HIP(launch_to_canonical(field_rhs(E->x, slot), x, E->st));
     if (info) {
         const CgScalars &c = sl.last;

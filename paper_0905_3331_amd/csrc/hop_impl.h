@@ -35,16 +35,6 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblk)
     return (bid & 7) * (nblk >> 3) + (bid >> 3);
 }
 
-// format of the solution correction updated by the fused CG epilogue
-template <class SP>
-struct XsOf {
-    using type = SpF32;
-};
-template <>
-struct XsOf<SpF64> {
-    using type = SpF64;
-};
-
 // (EP_CAN: EP_STORE to a canonical complex128 buffer)
 enum HopEp { EP_STORE = 0, EP_CG = 1, EP_RES = 2, EP_CAN = 3 };
 
@@ -102,9 +92,10 @@ struct HopArgs {
     long pstride;
     const CgScalars *scal;
     float one;  // 1.0, opaque to the compiler (see code_lo in fields.h)
-    // fused epilogues (EPI_K2_CG, EPI_K2_RES)
-    BatchView<SP> cg_r, cg_p;
-    BatchView<typename XsOf<SP>::type> cg_x;
+    // fused epilogues: r (EPI_K2_CG) or b (EPI_K2_RES), and the residual of
+    // EPI_K2_RES in its format
+    BatchView<SP> cg_r;
+    AnyView res;
     double2 *can_out;  // EP_CAN: the canonical output
     // batched 16-bit launches
     SiteDiv dv;
@@ -487,38 +478,28 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs<SP, LK> &a, const s
         }
     }
     if (EP == EP_CG) {
-        // CG update: x += alpha p ; r -= alpha (A p) ; |r|^2
-        using XS = typename XsOf<SP>::type;
-        using RX = typename XS::real;
-        const double al = a.scal[si].alpha;
-        const R ar = (R)al;
-        const RX ax = (RX)al;
-        spinor<R> rr, pp;
-        spinor<RX> xx;
+        // CG update: r -= alpha (A p) ; |r|^2
+        const R ar = (R)a.scal[si].alpha;
+        spinor<R> rr;
         a.cg_r.at(rhs).load(h, rr);
-        a.cg_p.at(rhs).load(h, pp);
-        a.cg_x.at(rhs).load(h, xx);
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
             for (int c = 0; c < 3; c++) {
-                xx.c[i][c].re = fmad(ax, (RX)pp.c[i][c].re, xx.c[i][c].re);
-                xx.c[i][c].im = fmad(ax, (RX)pp.c[i][c].im, xx.c[i][c].im);
                 rr.c[i][c].re = fmad(-ar, o.c[i][c].re, rr.c[i][c].re);
                 rr.c[i][c].im = fmad(-ar, o.c[i][c].im, rr.c[i][c].im);
             }
-        a.cg_x.at(rhs).store(h, xx);
         a.cg_r.at(rhs).store(h, rr);
         o = rr;
     } else if (EP == EP_RES) {
         // true residual r = b - A x
         spinor<R> bb;
-        a.cg_p.at(rhs).load(h, bb);
+        a.cg_r.at(rhs).load(h, bb);
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
             for (int c = 0; c < 3; c++) o.c[i][c] = bb.c[i][c] - o.c[i][c];
-        a.cg_r.at(rhs).store(h, o);
+        store_any(a.res, rhs, h, o);
     } else if (EP == EP_CAN) {
         // the site as it would be stored and read back
         if constexpr (SP::coded) SP::store_decoded(a.can_out + 12 * h, o);
@@ -1281,9 +1262,6 @@ void go16_e(const HopArgs<SP, L16R> &a, bool s, bool n, int ep, dim3 grid, dim3 
     if (ep == EP_CG)
         hipLaunchKernelGGL((hop16_kernel<SP, true, true, ORD, SB, EP_CG, ND, PM, false, BATCH, TWO>), grid, block, lds, st,
                            a);
-    else if (ep == EP_RES)
-        hipLaunchKernelGGL((hop16_kernel<SP, true, true, ORD, SB, EP_RES, ND, PM, false, BATCH, TWO>), grid, block, lds,
-                           st, a);
     else if (ep == EP_CAN) {
         // (a single field's K2, no norm)
         if constexpr (!ND && !BATCH)
@@ -1371,9 +1349,11 @@ void go_nd(const HopArgs<SP, LK> &a, bool s, bool n, int ep, dim3 grid, dim3 blo
 {
     if (ep == EP_CG)
         hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, false, 1, EP_CG, true>), grid, block, lds, st, a);
-    else if (ep == EP_RES)
-        hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, false, 1, EP_RES, true>), grid, block, lds, st, a);
-    else if (s && n)
+    else if (ep == EP_RES) {
+        if constexpr (__is_same(SP, SpF64))
+            hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, false, 1, EP_RES, true>), grid, block, lds, st,
+                               a);
+    } else if (s && n)
         hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, false, 1, EP_STORE, true>), grid, block, lds, st,
                            a);
     else if (s)
@@ -1389,9 +1369,10 @@ void go_w(const HopArgs<SP, LK> &a, bool s, bool n, int ep, dim3 grid, dim3 bloc
 {
     if (ep == EP_CG)
         hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, SB, G, EP_CG>), grid, block, lds, st, a);
-    else if (ep == EP_RES)
-        hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, SB, G, EP_RES>), grid, block, lds, st, a);
-    else if (s && n)
+    else if (ep == EP_RES) {
+        if constexpr (__is_same(SP, SpF64))
+            hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, SB, G, EP_RES>), grid, block, lds, st, a);
+    } else if (s && n)
         hipLaunchKernelGGL((hop_kernel<SP, LK, true, true, NT, ORD, SB, G, EP_STORE>), grid, block, lds, st, a);
     else if (s)
         hipLaunchKernelGGL((hop_kernel<SP, LK, true, false, NT, ORD, SB, G, EP_STORE>), grid, block, lds, st, a);
@@ -1432,8 +1413,8 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
         // fused epilogues: the vectors must be given, in the right formats, the
         // norm asked for, and (for CG) the device scalars holding alpha
         if (!cg || !partial || (ep == EP_CG && !scal)) return hipErrorInvalidValue;
-        if (cg->r.prec != in.prec || cg->p.prec != in.prec) return hipErrorInvalidValue;
-        if (ep == EP_CG && cg->x.prec != (in.prec == P64 ? P64 : P32)) return hipErrorInvalidValue;
+        if ((ep == EP_CG ? cg->r : cg->b).prec != in.prec) return hipErrorInvalidValue;
+        if (ep == EP_RES && in.prec != P64) return hipErrorInvalidValue;  // true residuals are FP64
     }
     static_assert(sizeof(HopArgs<SP, LK>) <= 4096, "kernel arguments are limited to 4 KB");
     HopArgs<SP, LK> a;
@@ -1454,9 +1435,8 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
     a.scal = scal;
     a.one = 1.0f;
     if (ep == EP_CG || ep == EP_RES) {
-        a.cg_r = make_bv<SP>(cg->r);
-        a.cg_p = make_bv<SP>(cg->p);
-        if (ep == EP_CG) a.cg_x = make_bv<typename XsOf<SP>::type>(cg->x);
+        a.cg_r = make_bv<SP>(ep == EP_CG ? cg->r : cg->b);
+        if (ep == EP_RES) a.res = make_any(cg->r);
     }
     if (ALL != hop_all_variants(in.prec, lk.fmt)) return hipErrorInvalidValue;  // tables out of step
     int variant = tu.variant;

@@ -52,8 +52,8 @@ struct SplitArgs {
     double *partial;  // of this right-hand side
     const CgScalars *scal;
     float one;  // 1.0, opaque to the compiler (see code_lo in fields.h)
-    SP cg_r, cg_p;
-    typename XsOf<SP>::type cg_x;
+    SP cg_r;      // fused epilogues: r (CG update) or b (true residual)
+    AnyView res;  // the true residual, in its format
     const double2 *cin, *cself;  // canonical operands (SplitCan)
     double2 *cout;
     SiteDiv dv;
@@ -173,44 +173,10 @@ struct SplitIo<Sp16<BF>> {
     }
 };
 
-// unit u of the solution vector of the fused CG update: UC components of an
-// FP64 field (FP64 hops) or an FP32 field
-template <int UC>
-__device__ __forceinline__ void load_x(const SpF64 &f, long h, int u, cx<double> (&v)[UC])
-{
-#pragma unroll
-    for (int k = 0; k < UC; k++) {
-        const double2 a = f.p[aidx(h, UC * u + k, 12)];
-        v[k] = {a.x, a.y};
-    }
-}
-template <int UC>
-__device__ __forceinline__ void store_x(const SpF64 &f, long h, int u, const cx<double> (&v)[UC])
-{
-#pragma unroll
-    for (int k = 0; k < UC; k++) f.p[aidx(h, UC * u + k, 12)] = make_double2(v[k].re, v[k].im);
-}
-template <int UC>
-__device__ __forceinline__ void load_x(const SpF32 &f, long h, int u, cx<float> (&v)[UC])
-{
-#pragma unroll
-    for (int k = 0; k < UC; k += 2) {
-        const float4 a = f.p[aidx(h, (UC * u + k) / 2, 6)];
-        v[k] = {a.x, a.y}, v[k + 1] = {a.z, a.w};
-    }
-}
-template <int UC>
-__device__ __forceinline__ void store_x(const SpF32 &f, long h, int u, const cx<float> (&v)[UC])
-{
-#pragma unroll
-    for (int k = 0; k < UC; k += 2)
-        f.p[aidx(h, (UC * u + k) / 2, 6)] = make_float4(v[k].re, v[k].im, v[k + 1].re, v[k + 1].im);
-}
-
 // hop (MU, DIR) of the sum from the loaded neighbour: the half spinor w, and
 // for 16-bit spinors the factor sc it is accumulated with
-template <int MU, int DIR, class SP, class LK, typename R>
-__device__ __forceinline__ void split_hop(const SplitArgs<SP, LK> &a, const typename LK::Loaded &u,
+template <int MU, int DIR, template <class, class> class A, class SP, class LK, typename R>
+__device__ __forceinline__ void split_hop(const A<SP, LK> &a, const typename LK::Loaded &u,
                                           const typename SplitIo<SP>::Raw &r, half<R> &w, float &sc)
 {
     const bool phase = (a.phase_mask >> MU) & 1;  // uniform over the launch
@@ -305,10 +271,7 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
     const int lane = p.lane;
     const uint32_t h = p.h;
     // what the unit needs of its own site, asked for with the hop's operands
-    cx<R> sf[UC], rr[UC], pp[UC];
-    using XS = typename XsOf<SP>::type;
-    using RX = typename XS::real;
-    cx<RX> xx[UC];
+    cx<R> sf[UC], rr[UC];
     if (p.active) {
         // the wavefront's neighbour (eo index hn; x coordinate xn) and link
         uint32_t hn, xn = p.x;
@@ -348,12 +311,7 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
             } else if (SELF) {
                 IO::load_unit(a.self, h, W, sf);
             }
-            if (EP == EP_CG) {
-                IO::load_unit(a.cg_r, h, W, rr);
-                IO::load_unit(a.cg_p, h, W, pp);
-                load_x<UC>(a.cg_x, h, W, xx);
-            }
-            if (EP == EP_RES) IO::load_unit(a.cg_p, h, W, pp);
+            if (EP == EP_CG || EP == EP_RES) IO::load_unit(a.cg_r, h, W, rr);
         }
         half<R> hv;
         float sc = 0.f;
@@ -403,16 +361,12 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
                 o[N] = fma(A, sf[N], B * acc);
             }
             if constexpr (EP == EP_CG) {
-                // x += alpha p ; r -= alpha (A p)
-                const double al = a.scal[a.rhs].alpha;
-                const R ar = (R)al;
-                const RX ax = (RX)al;
-                xx[N].re = fmad(ax, (RX)pp[N].re, xx[N].re);
-                xx[N].im = fmad(ax, (RX)pp[N].im, xx[N].im);
+                // r -= alpha (A p)
+                const R ar = (R)a.scal[a.rhs].alpha;
                 o[N].re = fmad(-ar, o[N].re, rr[N].re);
                 o[N].im = fmad(-ar, o[N].im, rr[N].im);
             }
-            if constexpr (EP == EP_RES) o[N] = pp[N] - o[N];
+            if constexpr (EP == EP_RES) o[N] = rr[N] - o[N];
             if constexpr (NORM) n2[N] = norm2(o[N]);
             if constexpr (SP::coded) {
                 const float f0 = fabsf(o[N].re), f1 = fabsf(o[N].im);
@@ -427,8 +381,14 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
                 comp(std::integral_constant<int, 2>{});
                 comp(std::integral_constant<int, 3>{});
             }
-            if constexpr (EP == EP_CG) store_x<UC>(a.cg_x, h, W, xx);
-            if constexpr (SP::coded)
+            if constexpr (EP == EP_RES) {
+                // (FP64 and FP32 residuals from here, 16-bit ones below: they need the whole site)
+                if (a.res.prec == P64)
+                    SplitIo<SpF64>::store_unit(SpF64{(double2 *)a.res.data}, h, W, o);
+                else if (a.res.prec == P32)
+                    st<false>((float4 *)a.res.data + aidx(h, W, 6),
+                              make_float4((float)o[0].re, (float)o[0].im, (float)o[1].re, (float)o[1].im));
+            } else if constexpr (SP::coded)
                 S.shm[W][lane] = m;
             else if constexpr (CAN & CAN_OUT)
                 IO::to_canonical(a.cout + 12L * p.site<(CAN & CAN_FULL) != 0>() + W * UC, o, 0.f);
@@ -440,11 +400,19 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
         __syncthreads();  // the sums are read, the largest magnitudes written
         // |out|^2 per component, for the sum over a site in the order of its components
         R *shn = (R *)S.sh;
+        // a 16-bit residual: the site's values (rounded to FP32 first, as Sp16::store does)
+        float2 *shr = (float2 *)(shn + 12 * SPLIT_SITES);
+        const bool res16 = EP == EP_RES && a.res.prec != P64 && a.res.prec != P32;
         if constexpr (UNIT) {
             if (p.active) {
                 if constexpr (NORM)
 #pragma unroll
                     for (int n = 0; n < UC; n++) shn[(W * UC + n) * SPLIT_SITES + lane] = n2[n];
+                if constexpr (EP == EP_RES)
+                    if (res16)
+#pragma unroll
+                        for (int n = 0; n < UC; n++)
+                            shr[(W * UC + n) * SPLIT_SITES + lane] = make_float2((float)o[n].re, (float)o[n].im);
                 if constexpr (SP::coded) {
                     const float mx = fmaxf(S.shm[0][lane], fmaxf(S.shm[1][lane], S.shm[2][lane]));
                     if constexpr (CAN & CAN_OUT)
@@ -456,6 +424,18 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
         }
         if constexpr (NORM) {
             __syncthreads();
+            if constexpr (EP == EP_RES && W == 1) {
+                // (wavefront 0 sums the norm meanwhile)
+                if (res16 && p.active) {
+                    spinor<float> v;
+#pragma unroll
+                    for (int c = 0; c < 12; c++) {
+                        const float2 q = shr[c * SPLIT_SITES + lane];
+                        v.c[c / 3][c % 3] = {q.x, q.y};
+                    }
+                    store_any(a.res, 0, h, v);
+                }
+            }
             if constexpr (W == 0) {
                 double s = 0.0;
                 if (p.active) {
@@ -471,19 +451,16 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
     }
 }
 
-template <class SP, class LK, bool SELF, bool NORM, int EP, int CAN = 0>
-__global__ __launch_bounds__(SPLIT_THREADS) void hop_split_kernel(SplitArgs<SP, LK> a)
+// the site of a lane, and the index of its block's (first) partial sum: a
+// 64-site tile is a quarter of a block of hop_kernel, or half of one with two
+// lanes per site (LPS), whose wavefronts leave their sums at PARTS * block +
+// wavefront
+template <int LPS, class A>
+__device__ __forceinline__ void split_site(const A &a, SplitSite &p)
 {
-    if (a.scal && a.scal[a.rhs].done) return;
-    __shared__ SplitShared<SP> S;
     const Geom &g = a.g;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t j = blockIdx.x & 7, sb = blockIdx.x >> 3;
-
-    // the site of the lane, and the index of the block's partial sum: a 64-site
-    // tile is a quarter of a block of hop_kernel, whose wavefronts leave their
-    // sums at PARTS * block + wavefront
-    SplitSite p;
+    constexpr uint32_t TPB = PARTS / LPS;  // tiles of such a block
     p.lane = threadIdx.x & 63;
     const uint32_t XH = (uint32_t)g.XH, LY = (uint32_t)g.LY, LZ = (uint32_t)g.LZ, T = (uint32_t)g.T;
     const uint32_t plane = LY * XH;
@@ -496,7 +473,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void hop_split_kernel(SplitArgs<SP, 
         p.y = r - r1 * LY;
         p.t = fdiv(r1, a.dv.lz);
         p.z = r1 - p.t * LZ;
-        p.pidx = lb;
+        p.pidx = LPS * lb;
     } else {
         // slabs of z (t outermost) or of t (z outermost), an extent in 8 parts
         const bool zs = a.ord == ORD_ZSLAB;
@@ -512,10 +489,20 @@ __global__ __launch_bounds__(SPLIT_THREADS) void hop_split_kernel(SplitArgs<SP, 
         p.xh = r2 - p.y * XH;
         p.t = zs ? o : e0 + e;
         p.z = zs ? e0 + e : o;
-        p.pidx = PARTS * (8 * (sb / PARTS) + j) + sb % PARTS;
+        p.pidx = PARTS * (8 * (sb / TPB) + j) + LPS * (sb % TPB);
     }
     p.h = ((p.t * LZ + p.z) * LY + p.y) * XH + p.xh;
     p.x = 2 * p.xh + ((a.out_par + p.t + p.z + p.y) & 1);  // (t + z + y + x) = out_par mod 2
+}
+
+template <class SP, class LK, bool SELF, bool NORM, int EP, int CAN = 0>
+__global__ __launch_bounds__(SPLIT_THREADS) void hop_split_kernel(SplitArgs<SP, LK> a)
+{
+    if (a.scal && a.scal[a.rhs].done) return;
+    __shared__ SplitShared<SP> S;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    SplitSite p;
+    split_site<1>(a, p);
     // (the eight roles run through the same barriers)
     switch (w) {
     case 0: split_role<0, SP, LK, SELF, NORM, EP, CAN>(a, S, p); break;
@@ -558,9 +545,8 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
     a.scal = scal;
     a.one = 1.0f;
     if (ep != EP_STORE) {
-        a.cg_r = field(cg->r);
-        a.cg_p = field(cg->p);
-        if (ep == EP_CG) a.cg_x = make_sp<typename XsOf<SP>::type>(field_rhs(cg->x, r));
+        a.cg_r = field(ep == EP_CG ? cg->r : cg->b);
+        if (ep == EP_RES) a.res = make_any(field_rhs(cg->r, r));
     }
     // canonical operands: the input with the own-site field (if any), the output
     const bool fused = ep != EP_STORE, sl = self.data != nullptr;
@@ -607,9 +593,10 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
     }
     if (ep == EP_CG)
         hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, true, EP_CG>), grid, block, 0, st, a);
-    else if (ep == EP_RES)
-        hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, true, EP_RES>), grid, block, 0, st, a);
-    else if (s && n)
+    else if (ep == EP_RES) {
+        if constexpr (__is_same(SP, SpF64))
+            hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, true, EP_RES>), grid, block, 0, st, a);
+    } else if (s && n)
         hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, true, EP_STORE>), grid, block, 0, st, a);
     else if (s)
         hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, false, EP_STORE>), grid, block, 0, st, a);

@@ -109,11 +109,11 @@ struct OpParams {
 //   EPI_FULL out = g5 [(1 + sigma i mut g5) self - kappa acc]              (eq. (eo1))
 //   EPI_SRC  out = self + kappa acc                                       (even/odd source, App. B)
 //   EPI_REC  out = (1 - sigma i mut g5)/(1+mut^2) (self + kappa acc)      (even-site solution, App. B)
-//   EPI_K2_CG  as EPI_K2, then the CG update with the RHS's alpha (device
-//              scalars): r -= alpha out ; x += alpha p ; norm of the new r; out is
-//              not stored
+//   EPI_K2_CG  as EPI_K2, then the CG update of the residual with the RHS's
+//              alpha (device scalars): r -= alpha out ; norm of the new r; out
+//              is not stored (x += alpha p goes with the update of p)
 //   EPI_K2_RES as EPI_K2, then r = b - out (the true residual) with its norm;
-//              out is not stored
+//              out is not stored, r is stored in any spinor format
 // For a doublet (OpParams::nd) a lane pair holds the two flavours (f, f') of
 // a site and, with A = 1 + sigma i mubar g5 tau^3 + epsbar tau^1 the site term
 // and d = 1 + mubar^2 - epsbar^2,
@@ -123,10 +123,10 @@ struct OpParams {
 // the norm is over both flavours.  Other epilogues are refused.
 enum HopEpi { EPI_K1 = 0, EPI_K2 = 1, EPI_FULL = 2, EPI_K2_CG = 3, EPI_K2_RES = 4, EPI_SRC = 5, EPI_REC = 6 };
 
-// Vectors of the fused epilogues: r and p in the hop's spinor format (p is b
-// for EPI_K2_RES), x in FP32 (FP64 for an FP64 hop).
+// Vectors of the fused epilogues: r (in the hop's spinor format for
+// EPI_K2_CG), and for EPI_K2_RES b in the hop's format.
 struct CgFields {
-    FieldDesc r, p, x;
+    FieldDesc r, b;
 };
 
 // Device scalars of a CG solve (one struct per right-hand side).
@@ -143,6 +143,8 @@ struct CgScalars {
     int reliable;    // number of true-residual recomputations
     int last_true;   // 1 if rr is a recomputed true residual
     int pad;
+    int xpend;       // 1: x += alpha p of the last iteration is still to be done
+    int fresh;       // 1: the solution (correction) holds nothing yet and counts as zero
 };
 
 constexpr int HOP_BLOCK = 256;
@@ -250,17 +252,26 @@ hipError_t launch_zero(const FieldDesc &v, const RhsList &rl, hipStream_t st);
 hipError_t launch_axpy_norm(const FieldDesc &x, const FieldDesc &p, const FieldDesc &r, const FieldDesc &ap,
                             const RhsList &rl, const CgScalars *scal, double *partial, long pstride,
                             bool skip_done, hipStream_t st);
-// p = r + beta p
-hipError_t launch_xpay(const FieldDesc &r, const FieldDesc &p, const RhsList &rl, const CgScalars *scal,
-                       bool skip_done, hipStream_t st);
+// x += alpha p where that is pending (xpend; x may have no data: nothing), then
+// p = r + beta p (not for done RHS if skip_done, not at all if only_x)
+hipError_t launch_xpay(const FieldDesc &r, const FieldDesc &p, const FieldDesc &x, const RhsList &rl,
+                       const CgScalars *scal, bool skip_done, bool only_x, hipStream_t st);
 // r = b - ax (FP64), partial |r|^2
 hipError_t launch_residual(const FieldDesc &b, const FieldDesc &ax, const FieldDesc &r, const RhsList &rl,
                            double *partial, long pstride, hipStream_t st);
 // out = cu in (spins 0, 1), cd in (spins 2, 3); FP64 fields
 hipError_t launch_twist(const FieldDesc &in, const FieldDesc &out, const RhsList &rl, double2 cu, double2 cd,
                         hipStream_t st);
-// x64 += xs ; xs = 0
-hipError_t launch_accumulate(const FieldDesc &x64, const FieldDesc &xs, const RhsList &rl, hipStream_t st);
+// x64 += xs, with the pending xs += alpha p; x64 counts as zero before the first
+// true residual, xs while it is fresh
+hipError_t launch_accumulate(const FieldDesc &x64, const FieldDesc &xs, const FieldDesc &p, const RhsList &rl,
+                             const CgScalars *scal, hipStream_t st);
+// x += d (FP64)
+hipError_t launch_add(const FieldDesc &x, const FieldDesc &d, const RhsList &rl, hipStream_t st);
+// a right-hand side enters a solve: b (FP64), r and p (one format) of RHS 0 of
+// each field from the canonical source, and the partials of |b|^2
+hipError_t launch_join(const double2 *src, const FieldDesc &b, const FieldDesc &r, const FieldDesc &p, double *partial,
+                       hipStream_t st);
 
 // Scalar kernels (one block per RHS): deterministic sums of the partials of nparts blocks.
 enum ScalarOp {
@@ -269,11 +280,14 @@ enum ScalarOp {
     SC_BETA = 2,     // rr_prev = rr ; rr = sum ; beta = rr / rr_prev ; iter++ ; done = rr < target
     SC_RELIABLE = 3  // rr = sum (true residual) ; beta = rr / rr_prev ; done = rr < target
 };
+// defer: the solve leaves x += alpha p to launch_xpay: SC_INIT and SC_RELIABLE
+// set fresh to it (and xpend to 0), SC_BETA xpend (0 for a skipped RHS; an
+// update pending before was done by then, so x is not fresh any more).
 // publish != nullptr: the scalars of RHS r are finally copied to publish[r]
 // (host-mapped memory), also when the block is skipped.
 hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long pstride, int nparts,
-                         CgScalars *scal, double tol2, int relative, bool skip_done, CgScalars *publish,
-                         hipStream_t st);
+                         CgScalars *scal, double tol2, int relative, bool skip_done, bool defer,
+                         CgScalars *publish, hipStream_t st);
 // out[i] = sum of the partials of nparts blocks of RHS rl.idx[i], in the order of the scalar kernels
 hipError_t launch_sums(const RhsList &rl, const double *partial, long pstride, int nparts, double *out, hipStream_t st);
 // out[0] = deterministic maximum of partial[0..n)

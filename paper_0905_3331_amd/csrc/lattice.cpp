@@ -565,14 +565,13 @@ static double canonical_extra_bytes(const FieldDesc &in, const FieldDesc &self, 
     return (192.0 - sp) * ((in.layout != 0) + (self.data && self.layout != 0) + (out.data && out.layout != 0));
 }
 
-static double fused_extra_bytes(int prec, int epi)
+static double fused_extra_bytes(int prec, int epi, const CgFields *cg)
 {
     // the epilogue's own vectors beside the half-sweep's (whose output write
-    // stands for the write of r): CG reads r and p and reads and writes x;
-    // the residual reads b
-    const double sp = prec == P64 ? 192.0 : prec == P32 ? 96.0 : 52.0;
-    const double xsp = prec == P64 ? 192.0 : 96.0;
-    return epi == EPI_K2_CG ? (2 * sp + 2 * xsp) : epi == EPI_K2_RES ? sp : 0.0;
+    // stands for the write of r): CG reads r; the residual reads b, and its r
+    // may be of another format
+    auto bytes = [](int q) { return q == P64 ? 192.0 : q == P32 ? 96.0 : 52.0; };
+    return epi == EPI_K2_CG ? bytes(prec) : epi == EPI_K2_RES ? bytes(cg->r.prec) : 0.0;
 }
 
 // hop half-sweep of a batch of doublets (op.nd): the two flavours of a site
@@ -592,8 +591,7 @@ static int hop_nd(Lattice *L, int out_par, const FieldDesc &in, const FieldDesc 
     CgFields c2;
     if (cg) {
         c2.r = flavour_view(cg->r);
-        c2.p = flavour_view(cg->p);
-        c2.x = flavour_view(cg->x);
+        c2.b = flavour_view(cg->b);
     }
     RhsList fl;
     fl.n = 2 * rl.n;
@@ -625,7 +623,7 @@ static int hop_nd(Lattice *L, int out_par, const FieldDesc &in, const FieldDesc 
     if (L->timing) {
         t.a = pool_event(L);
         t.b = pool_event(L);
-        t.bytes = (hop_bytes_per_site(in.prec, lk.fmt, epi != EPI_K1, fl.n) + fused_extra_bytes(in.prec, epi) * fl.n) *
+        t.bytes = (hop_bytes_per_site(in.prec, lk.fmt, epi != EPI_K1, fl.n) + fused_extra_bytes(in.prec, epi, cg) * fl.n) *
                   (double)L->g.vh;
         t.flops = 1320.0 * (double)L->g.vh * fl.n;
         t.prec = in.prec;
@@ -711,7 +709,7 @@ int hop(Lattice *L, int out_par, const FieldDesc &in, const FieldDesc &self, con
     if (L->timing) {
         t.a = pool_event(L);
         t.b = pool_event(L);
-        t.bytes = (hop_bytes_per_site(in.prec, lk.fmt, epi != EPI_K1, rl.n) + fused_extra_bytes(in.prec, epi) * rl.n +
+        t.bytes = (hop_bytes_per_site(in.prec, lk.fmt, epi != EPI_K1, rl.n) + fused_extra_bytes(in.prec, epi, cg) * rl.n +
                    canonical_extra_bytes(in, self, out)) *
                   (double)L->g.vh;
         t.flops = 1320.0 * (double)L->g.vh * rl.n;
@@ -756,7 +754,7 @@ int residual_QhatQhat(Lattice *L, const OpParams &op, const FieldDesc &x, const 
     const FieldDesc none{};
     CgFields cg;
     cg.r = r;
-    cg.p = b;
+    cg.b = b;
     TMQ_TRY(apply_Qhat(L, op, -1, x, tmp_o, tmp_e, lk, rl, nullptr, nullptr, st));
     TMQ_TRY(hop(L, 0, tmp_o, none, tmp_e, lk, op, EPI_K1, +1, rl, nullptr, nullptr, st));
     TMQ_TRY(hop(L, 1, tmp_e, tmp_o, none, lk, op, EPI_K2_RES, +1, rl, partial, nullptr, st, &cg));

@@ -359,7 +359,7 @@ int solve_M_batch(Lattice *L, const tmq_params &p, int sign, const tmq_solver_op
         }
         // d_e = (M_ee)^-1 (r_e + kappa H_eo d_o) ; psi += d
         TMQ_TRY(hop(L, 0, dd, re, de, lk, op, EPI_REC, sign, al, nullptr, nullptr, st));
-        TMQ_HIP(launch_accumulate(fpsi, fd, al, st));
+        TMQ_HIP(launch_add(fpsi, fd, al, st));
         // r = phi - M psi = g5 (g5 phi - Q psi)
         TMQ_TRY(apply_Q_full(L, op, sign, fpsi, fq, lk, al, st));
         TMQ_HIP(launch_residual(fphi, fq, fg, al, L->partial[2], L->pstride, st));
@@ -489,11 +489,12 @@ int solve_full(Lattice *L, const tmq_params &p, const tmq_solver_opts &o, const 
     // one CG iteration publishing its scalars to ring slot `slot`
     auto iterate = [&](int slot) -> int {
         TMQ_TRY(apply_A(pp, ap, L->partial[0]));
-        TMQ_HIP(launch_scalar(SC_ALPHA, one, L->partial[0], ps, blas_grid(n), S, 0, 0, true, nullptr, st));
+        TMQ_HIP(launch_scalar(SC_ALPHA, one, L->partial[0], ps, blas_grid(n), S, 0, 0, true, false, nullptr,
+                              st));
         TMQ_HIP(launch_axpy_norm(x, pp, r, ap, one, S, L->partial[1], ps, true, st));
-        TMQ_HIP(launch_scalar(SC_BETA, one, L->partial[1], ps, blas_grid(n), S, 0, 0, true,
+        TMQ_HIP(launch_scalar(SC_BETA, one, L->partial[1], ps, blas_grid(n), S, 0, 0, true, false,
                               L->ring_dev + (size_t)slot * MAX_RHS, st));
-        TMQ_HIP(launch_xpay(r, pp, one, S, true, st));
+        TMQ_HIP(launch_xpay(r, pp, FieldDesc{}, one, S, true, false, st));
         return TMQ_OK;
     };
     hipGraph_t graph[2] = {nullptr, nullptr};
@@ -527,7 +528,8 @@ int solve_full(Lattice *L, const tmq_params &p, const tmq_solver_opts &o, const 
     TMQ_HIP(launch_zero(x, one, st));
     TMQ_HIP(launch_convert(b, r, one, st));
     TMQ_HIP(launch_norm2(r, one, L->partial[1], ps, st));
-    TMQ_HIP(launch_scalar(SC_INIT, one, L->partial[1], ps, blas_grid(n), S, tol2, o.relative, false, nullptr, st));
+    TMQ_HIP(launch_scalar(SC_INIT, one, L->partial[1], ps, blas_grid(n), S, tol2, o.relative, false, false, nullptr,
+                          st));
     TMQ_HIP(launch_convert(r, pp, one, st));
     std::vector<CgScalars> cur;
     TMQ_TRY(read_scalars(L, 1, st, cur));
@@ -580,11 +582,11 @@ int solve_full(Lattice *L, const tmq_params &p, const tmq_solver_opts &o, const 
         // true residual r = b - A x
         TMQ_TRY(apply_A(x, ap, nullptr));
         TMQ_HIP(launch_residual(b, ap, r, one, L->partial[2], ps, st));
-        TMQ_HIP(launch_scalar(SC_RELIABLE, one, L->partial[2], ps, blas_grid(n), S, tol2, o.relative, false, nullptr,
-                              st));
+        TMQ_HIP(launch_scalar(SC_RELIABLE, one, L->partial[2], ps, blas_grid(n), S, tol2, o.relative, false, false,
+                              nullptr, st));
         TMQ_TRY(read_scalars(L, 1, st, cur));
         if (cur[0].nan || cur[0].done || enq >= max_iter) break;
-        TMQ_HIP(launch_xpay(r, pp, one, S, false, st));
+        TMQ_HIP(launch_xpay(r, pp, FieldDesc{}, one, S, false, false, st));
     }
     int status = TMQ_OK;
     if (cur[0].nan) {

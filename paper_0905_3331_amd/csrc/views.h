@@ -51,6 +51,40 @@ inline BatchView<SP> make_bv(const FieldDesc &f)
     return BatchView<SP>{make_sp<SP>(f), f.rhs_elems, f.rhs_sites};
 }
 
+// a batched field whose format is known at run time
+struct AnyView {
+    void *data;
+    float *scale;
+    long rhs_elems, rhs_sites;
+    int prec;
+};
+inline AnyView make_any(const FieldDesc &f) { return AnyView{f.data, f.scale, f.rhs_elems, f.rhs_sites, f.prec}; }
+// site h of RHS r stored in the view's format (the format is uniform over the launch)
+template <typename R>
+__device__ __forceinline__ void store_any(const AnyView &v, int r, long h, const spinor<R> &s)
+{
+    if (v.prec == P64)
+        SpF64{(double2 *)v.data + r * v.rhs_elems}.store(h, s);
+    else if (v.prec == P32)
+        SpF32{(float4 *)v.data + r * v.rhs_elems}.store(h, s);
+    else if (v.prec == P16)
+        SpH16{(uint4 *)v.data + r * v.rhs_elems, v.scale + r * v.rhs_sites}.store(h, s);
+    else {
+        // (values of its own: the FP16 codes are formed by one instruction that
+        // multiplies by 1 / scale and rounds once, which a product shared with
+        // this branch would keep the compiler from using)
+        spinor<float> t;
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                t.c[i][c] = {(float)s.c[i][c].re, (float)s.c[i][c].im};
+                asm("" : "+v"(t.c[i][c].re), "+v"(t.c[i][c].im));
+            }
+        SpB16{(uint4 *)v.data + r * v.rhs_elems, v.scale + r * v.rhs_sites}.store(h, t);
+    }
+}
+
 // dispatch a statement over the four spinor formats (F is the format type)
 #define TMQ_DISPATCH_SP(prec, F, ...)                      \
     switch (prec) {                                        \
