@@ -1402,6 +1402,12 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
                         const LinkDesc &lk, const OpParams &op, int epi, int sign, const RhsList &rl, double *partial,
                         long pstride, const CgScalars *scal, int ord, int nblk, hipStream_t st, const CgFields *cg);
 
+template <class SP, class LK>
+hipError_t launch_split_nd(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &self,
+                           const FieldDesc &out, const LinkDesc &lk, const OpParams &op, int epi, int sign,
+                           const RhsList &rl, double *partial, long pstride, const CgScalars *scal, int ord, int nblk,
+                           hipStream_t st, const CgFields *cg);
+
 template <class SP, class LK, bool ALL, bool MULTI>
 hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &self, const FieldDesc &out,
               const LinkDesc &lk, const OpParams &op, int epi, int sign, const RhsList &rl, double *partial,
@@ -1480,6 +1486,12 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
         const bool s = epi != EPI_K1, n = partial != nullptr;
         if (s && !self.data) return hipErrorInvalidValue;
         if (!s && n) return hipErrorInvalidValue;
+        if constexpr (ALL && !SP::coded) {
+            // one FP64 or FP32 doublet: the split kernel, with the sums of the lane pairs
+            if (rl.n == 2)
+                return launch_split_nd<SP, LK>(g, out_par, in, self, out, lk, op, epi, sign, rl, partial, pstride, scal,
+                                               hop_order(variant), hop_grid_variant(g, variant, 2), st, cg);
+        }
         const int lanes = hop_nd_lanes(g, in.prec, lk.fmt, op);  // per doublet site
         a.nblk = hop_grid_variant(g, variant, lanes);
         const int ntup = rl.n / 2;

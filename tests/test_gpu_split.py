@@ -132,3 +132,30 @@ def test_canonical_buffers_in_place(tmq, dims):  # noqa: F811
     lat.apply_Q_full(p, +1, v, out=v)
     assert torch.equal(v, out)
     lat.close()
+
+
+@pytest.mark.parametrize("variant", [0, 1, 3])
+@pytest.mark.parametrize("dims", EDGES[:4], ids=lambda d: "x".join(map(str, d)))
+def test_split_doublet(tmq, dims, variant, monkeypatch):  # noqa: F811
+    """One FP64 or FP32 doublet runs the split kernel, a batch the lane pairs:
+    the operator against the oracle, and solves of both inner precisions (and of
+    16-bit ones, whose true residual is the split FP64 kernel's) equal in a
+    batch and alone."""
+    monkeypatch.setenv("TMQ_HOP_VARIANT", str(variant))
+    U = synth.random_gauge(dims, seed=305)
+    lat = tmq.Lattice(dims)
+    lat.load_gauge(U)
+    V = int(np.prod(dims))
+    bs = [dev(synth.gaussian_spinor((2, V // 2, 4, 3), seed=37 + i)) for i in range(2)]
+    ps = [tmq.nd_params(0.15, 0.11, 0.09, THETA_GEN), tmq.nd_params(0.14, 0.05, 0.12, THETA_GEN)]
+    ref = oracle.Qhat_nd(U, host(bs[0]), 0.15, 0.11, 0.09, +1, THETA_GEN)
+    for prec, tol in (("fp64", 1e-13), ("fp32", 2e-6)):
+        got = host(lat.apply_Qhat_nd(ps[0], +1, bs[0], prec=prec))
+        assert rel(got, ref) < tol and site_err(got, ref) < SITE_BOUND[prec], (prec, rel(got, ref))
+    for sloppy in ("fp64", "fp32", "fp16"):
+        opts = tmq.solver_opts(tol=1e-9, sloppy=sloppy, sloppy_link="fp32" if sloppy == "fp32" else "fp16")
+        xs, infos = lat.solve_nd_batch(ps, bs, opts)
+        for i in range(2):
+            x, info = lat.solve_nd(ps[i], bs[i], opts)
+            assert info.status == 0 and info.iters == infos[i].iters and torch.equal(x, xs[i]), (sloppy, i)
+    lat.close()
