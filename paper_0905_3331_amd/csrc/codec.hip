@@ -12,6 +12,7 @@
 // value * (1 / scale) in FP32.
 #include <type_traits>
 
+#include "canonical.h"
 #include "devutil.h"
 #include "views.h"
 
@@ -62,23 +63,6 @@ __device__ __forceinline__ void store_f64<SpB16>(const SpB16 &f, long h, const s
     store_f64_16<true>(f, h, s);
 }
 
-__device__ __forceinline__ void load_canonical(const double2 *in, long site, spinor<double> &s)
-{
-    const double2 *q = in + site * 12;
-#pragma unroll
-    for (int k = 0; k < 12; k++) {
-        double2 v = q[k];
-        s.c[k / 3][k % 3] = cx<double>{v.x, v.y};
-    }
-}
-
-__device__ __forceinline__ void store_canonical(double2 *out, long site, const spinor<double> &s)
-{
-    double2 *q = out + site * 12;
-#pragma unroll
-    for (int k = 0; k < 12; k++) q[k] = make_double2(s.c[k / 3][k % 3].re, s.c[k / 3][k % 3].im);
-}
-
 template <class SP>
 __global__ __launch_bounds__(BLAS_BLOCK) void k_from_canonical(const double2 *in, SP out, long n)
 {
@@ -99,19 +83,6 @@ __global__ __launch_bounds__(BLAS_BLOCK) void k_to_canonical(SP in, double2 *out
         in.load(h, s);
         store_canonical(out, h, s);
     }
-}
-
-// parity of canonical site s
-__device__ __forceinline__ int site_parity(const Geom &g, long s)
-{
-    const unsigned su = (unsigned)s;
-    const unsigned x = su % (unsigned)g.LX;
-    unsigned r = su / (unsigned)g.LX;
-    const unsigned y = r % (unsigned)g.LY;
-    r /= (unsigned)g.LY;
-    const unsigned z = r % (unsigned)g.LZ;
-    const unsigned t = r / (unsigned)g.LZ;
-    return (int)((t + z + y + x) & 1u);
 }
 
 template <class SP, bool TO>

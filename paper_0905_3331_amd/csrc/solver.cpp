@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "engine.h"
+#include "invert.h"
 
 namespace tmq {
 
@@ -237,24 +238,10 @@ int solve_qhat_bicgstab(Lattice *L, const tmq_params &p, int sign, const tmq_sol
 
 // ------------------------------------------- M psi = phi through even/odd
 
-
-
-// Solve M^{sign} psi = phi (full lattice, canonical device buffers) with the
-// even/odd factorisation of the inversion in App. B:
-//   phi'_e = (M_ee)^-1 phi_e,  phi'_o = phi_o - M_oe (M_ee)^-1 phi_e,
-//   psi_o  = (M_oo - M_oe (M_ee)^-1 M_eo)^-1 phi'_o,
-//   psi_e  = phi'_e - (M_ee)^-1 M_eo psi_o = (M_ee)^-1 (phi_e + kappa H_eo psi_o),
-// with M_ee = 1 + sign i mut g5, M_eo = -kappa H_eo, M_oe = -kappa H_oe.  The
-// Schur complement is g5 Qhat^{sign} (eq. (eo4)), so psi_o solves
-// Qhat^{sign} psi_o = g5 phi'_o: psi_o = Qhat^- A^-1 g5 phi'_o for sign +1
-// and psi_o = A^-1 Qhat^+ g5 phi'_o for sign -1, A = Qhat^+ Qhat^- by CG.
-// The residual phi - M psi is recomputed in FP64 on the full lattice; while
-// it is above the tolerance the same steps solve for the correction.
-// per-RHS |v|^2 of the RHS in rl of a batched FP64 field (through L->partial[1])
-static int field_norms(Lattice *L, const FieldDesc &v, const RhsList &rl, hipStream_t st, std::vector<double> &out)
+// the sums of the partial sums in L->partial[2] of n sites of the RHS in rl (through L->partial[1])
+static int field_norms(Lattice *L, long n, const RhsList &rl, hipStream_t st, std::vector<double> &out)
 {
-    TMQ_HIP(launch_norm2(v, rl, L->partial[2], L->pstride, st));
-    TMQ_HIP(launch_sums(rl, L->partial[2], L->pstride, blas_grid(v.n), L->partial[1], st));
+    TMQ_HIP(launch_sums(rl, L->partial[2], L->pstride, blas_grid(n), L->partial[1], st));
     std::vector<double> sums((size_t)rl.n);
     TMQ_HIP(hipMemcpyAsync(sums.data(), L->partial[1], sizeof(double) * sums.size(), hipMemcpyDeviceToHost, st));
     TMQ_HIP(hipStreamSynchronize(st));
@@ -270,18 +257,26 @@ static RhsList rhs_list(const std::vector<int> &idx)
     return l;
 }
 
+// Solve M^{sign} psi = phi (full lattice, canonical device buffers) with the
+// even/odd factorisation of the inversion in App. B:
+//   phi'_e = (M_ee)^-1 phi_e,  phi'_o = phi_o - M_oe (M_ee)^-1 phi_e,
+//   psi_o  = (M_oo - M_oe (M_ee)^-1 M_eo)^-1 phi'_o,
+//   psi_e  = phi'_e - (M_ee)^-1 M_eo psi_o = (M_ee)^-1 (phi_e + kappa H_eo psi_o),
+// with M_ee = 1 + sign i mut g5, M_eo = -kappa H_eo, M_oe = -kappa H_oe.  The
+// Schur complement is g5 Qhat^{sign} (eq. (eo4)), so psi_o solves
+// Qhat^{sign} psi_o = g5 phi'_o: psi_o = Qhat^- A^-1 g5 phi'_o for sign +1
+// and psi_o = A^-1 Qhat^+ g5 phi'_o for sign -1, A = Qhat^+ Qhat^- by CG.
+// The residual phi - M psi is recomputed in FP64 on the full lattice; while
+// it is above the tolerance the same steps solve for the correction.
 int solve_M_batch(Lattice *L, const tmq_params &p, int sign, const tmq_solver_opts &o, int nb, const double2 *const *phi,
                   double2 *const *psi, hipStream_t st, tmq_solve_info *info)
 {
     const auto t0 = std::chrono::steady_clock::now();
     const long vh = L->g.vh, n = 2 * vh;
-    FieldDesc fphi, fpsi, fr, fd, fq, fg, te, to, wo, yo, bc, yc;
-    TMQ_TRY(work_field(L, "m_phi", P64, n, &fphi, nb));  // g5 phi
+    FieldDesc fpsi, fr, fd, fq, te, to, wo, yo, bc, yc;
     TMQ_TRY(work_field(L, "m_psi", P64, n, &fpsi, nb));
     TMQ_TRY(work_field(L, "m_r", P64, n, &fr, nb));      // source of the round (the residual)
-    TMQ_TRY(work_field(L, "m_d", P64, n, &fd, nb));      // solution of the round
     TMQ_TRY(work_field(L, "m_q", P64, n, &fq, nb));
-    TMQ_TRY(work_field(L, "m_g", P64, n, &fg, nb));
     TMQ_TRY(work_field(L, "m_te", P64, vh, &te, nb));
     TMQ_TRY(work_field(L, "m_to", P64, vh, &to, nb));
     TMQ_TRY(work_field(L, "m_wo", P64, vh, &wo, nb));
@@ -297,28 +292,38 @@ int solve_M_batch(Lattice *L, const tmq_params &p, int sign, const tmq_solver_op
     const double2 g5_u = make_double2(1.0, 0.0), g5_d = make_double2(-1.0, 0.0);
     const int max_rounds = 4;
 
-    for (int r = 0; r < nb; r++) TMQ_HIP(launch_full_from_canonical(L->g, phi[r], field_rhs(fr, r), st));
-    TMQ_HIP(launch_twist(fr, fphi, all, g5_u, g5_d, st));
-    TMQ_HIP(launch_zero(fpsi, all, st));
+    CanList phis{}, psis{};
+    for (int r = 0; r < nb; r++) {
+        phis.p[r] = const_cast<double2 *>(phi[r]);
+        psis.p[r] = psi[r];
+    }
+    TMQ_HIP(launch_m_enter(L->g, phis, fr, te, mee_u, mee_d, all, L->partial[2], L->pstride, st));
     std::vector<double> bb((size_t)nb), rr((size_t)nb), target((size_t)nb);
     std::vector<int> status((size_t)nb, TMQ_OK), iters((size_t)nb, 0), rus((size_t)nb, 0);
-    TMQ_TRY(field_norms(L, fr, all, st, bb));
-    std::vector<int> active;
+    TMQ_TRY(field_norms(L, n, all, st, bb));
+    std::vector<int> active, idle;
     for (int r = 0; r < nb; r++) {
         target[r] = o.relative ? o.tol * o.tol * bb[r] : o.tol * o.tol;
         rr[r] = bb[r];
-        if (rr[r] > target[r] && bb[r] > 0.0) active.push_back(r);
+        (rr[r] > target[r] && bb[r] > 0.0 ? active : idle).push_back(r);
     }
+    TMQ_HIP(launch_zero(fpsi, rhs_list(idle), st));
     for (int round = 0; !active.empty() && round < max_rounds; round++) {
         const RhsList al = rhs_list(active);
         const FieldDesc re = field_sub(fr, 0, vh), ro = field_sub(fr, vh, vh);
+        // the first solution is psi itself, a later one a correction to it
+        if (round == 0)
+            fd = fpsi;
+        else
+            TMQ_TRY(work_field(L, "m_d", P64, n, &fd, nb));
         const FieldDesc de = field_sub(fd, 0, vh), dd = field_sub(fd, vh, vh);
         // phi'_o = r_o + kappa H_oe (M_ee)^-1 r_e
-        TMQ_HIP(launch_twist(re, te, al, mee_u, mee_d, st));
+        if (round > 0) TMQ_HIP(launch_twist(re, te, al, mee_u, mee_d, st));
         TMQ_TRY(hop(L, 1, te, ro, wo, lk, op, EPI_SRC, sign, al, nullptr, nullptr, st));
         // odd system: Qhat^{sign} d_o = g5 phi'_o
-        TMQ_HIP(launch_twist(wo, to, al, g5_u, g5_d, st));
-        if (o.mode == TMQ_MODE_BICGSTAB) {
+        const bool cg = o.mode != TMQ_MODE_BICGSTAB;
+        if (!cg || sign < 0) TMQ_HIP(launch_twist(wo, to, al, g5_u, g5_d, st));
+        if (!cg) {
             // BiCGstab on Qhat^{sign} itself, one right-hand side at a time
             for (int r : active) {
                 tmq_solve_info ci{};
@@ -331,12 +336,11 @@ int solve_M_batch(Lattice *L, const tmq_params &p, int sign, const tmq_solver_op
         } else {
             // CG on Qhat^+ Qhat^- for all of them together
             if (sign < 0) TMQ_TRY(apply_Qhat(L, op, +1, to, wo, te, lk, al, nullptr, nullptr, st));
-            const FieldDesc &src = sign < 0 ? wo : to;
+            TMQ_HIP(launch_m_to_canonical(wo, bc, sign < 0 ? 1.0 : -1.0, al, st));
             std::vector<const double *> bp;
             std::vector<double *> yp;
             std::vector<tmq_params> pa;
             for (int r : active) {
-                TMQ_HIP(launch_to_canonical(field_rhs(src, r), (double2 *)field_rhs(bc, r).data, st));
                 bp.push_back((const double *)field_rhs(bc, r).data);
                 yp.push_back((double *)field_rhs(yc, r).data);
                 pa.push_back(p);
@@ -350,21 +354,17 @@ int solve_M_batch(Lattice *L, const tmq_params &p, int sign, const tmq_solver_op
                 iters[r] += ci[i].iters;
                 rus[r] += ci[i].reliable_updates;
                 if (ci[i].status != TMQ_OK) status[r] = ci[i].status;
-                TMQ_HIP(launch_from_canonical((const double2 *)field_rhs(yc, r).data, field_rhs(yo, r), st));
             }
-            if (sign > 0)
-                TMQ_TRY(apply_Qhat(L, op, -1, yo, dd, te, lk, al, nullptr, nullptr, st));
-            else
-                TMQ_HIP(launch_convert(yo, dd, al, st));
+            TMQ_HIP(launch_m_from_canonical(yc, sign > 0 ? yo : dd, al, st));
+            if (sign > 0) TMQ_TRY(apply_Qhat(L, op, -1, yo, dd, te, lk, al, nullptr, nullptr, st));
         }
         // d_e = (M_ee)^-1 (r_e + kappa H_eo d_o) ; psi += d
         TMQ_TRY(hop(L, 0, dd, re, de, lk, op, EPI_REC, sign, al, nullptr, nullptr, st));
-        TMQ_HIP(launch_add(fpsi, fd, al, st));
-        // r = phi - M psi = g5 (g5 phi - Q psi)
+        if (round > 0) TMQ_HIP(launch_add(fpsi, fd, al, st));
+        // r = phi - M psi = phi - g5 Q psi
         TMQ_TRY(apply_Q_full(L, op, sign, fpsi, fq, lk, al, st));
-        TMQ_HIP(launch_residual(fphi, fq, fg, al, L->partial[2], L->pstride, st));
-        TMQ_HIP(launch_twist(fg, fr, al, g5_u, g5_d, st));
-        TMQ_TRY(field_norms(L, fr, al, st, rr));
+        TMQ_HIP(launch_m_residual(L->g, phis, fq, fr, al, L->partial[2], L->pstride, st));
+        TMQ_TRY(field_norms(L, n, al, st, rr));
         std::vector<int> next;
         for (int r : active)
             if (status[r] == TMQ_OK && rr[r] > target[r]) next.push_back(r);
@@ -375,8 +375,8 @@ int solve_M_batch(Lattice *L, const tmq_params &p, int sign, const tmq_solver_op
         if (!std::isfinite(rr[r])) status[r] = TMQ_ENAN;
         if (status[r] == TMQ_OK && rr[r] > target[r]) status[r] = TMQ_ENOCONV;
         if (status[r] == TMQ_ENAN || (status[r] == TMQ_ENOCONV && worst == TMQ_OK)) worst = status[r];
-        TMQ_HIP(launch_full_to_canonical(L->g, field_rhs(fpsi, r), psi[r], st));
     }
+    TMQ_HIP(launch_m_leave(L->g, fpsi, psis, all, st));
     TMQ_HIP(hipStreamSynchronize(st));
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (info)

@@ -159,3 +159,35 @@ def test_split_doublet(tmq, dims, variant, monkeypatch):  # noqa: F811
             x, info = lat.solve_nd(ps[i], bs[i], opts)
             assert info.status == 0 and info.iters == infos[i].iters and torch.equal(x, xs[i]), (sloppy, i)
     lat.close()
+
+
+@pytest.mark.parametrize("sign", [+1, -1])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 2, 10), (8, 4, 4, 6)], ids=lambda d: "x".join(map(str, d)))
+def test_solve_M_batch_passes(tmq, dims, sign):  # noqa: F811
+    """Batched inversions with a zero source among them (its solution is zero,
+    whatever the work fields held before), sources left as they were, and every
+    tolerance met by the oracle's M: also the loose one, which a solve of the
+    normal equations to the same tolerance often misses at this mass, so that
+    correction rounds run."""
+    U = synth.random_gauge(dims, seed=303)
+    lat = tmq.Lattice(dims)
+    lat.load_gauge(U)
+    V = int(np.prod(dims))
+    e = np.zeros((V, 4, 3), np.complex128)
+    e[V // 2 + 1, 2, 1] = 1.0
+    phis = [synth.gaussian_spinor(dims + (4, 3), seed=61).reshape(V, 4, 3), np.zeros_like(e), e]
+    p = tmq.params(0.1632, 0.004, THETA)
+    for tol in (1e-10, 1e-3):
+        srcs = [dev(f) for f in phis]
+        psis, infos = lat.solve_M_batch(p, sign, srcs, tmq.solver_opts(tol=tol, sloppy="fp16", sloppy_link="fp16"))
+        for f, s, x, i in zip(phis, srcs, psis, infos):
+            assert np.array_equal(host(s), f)
+            if not f.any():
+                assert not host(x).any() and i.status == 0
+                continue
+            full = f.reshape(dims + (4, 3))
+            r = full - oracle.M(U, host(x).reshape(full.shape), 0.1632, 0.004, sign, THETA)
+            res = float(np.linalg.norm(r) / np.linalg.norm(f))
+            assert i.status == 0 and res <= tol * (1 + 1e-6), (tol, res)
+            assert abs(res - i.true_rel_residual) <= 1e-3 * res + 1e-16
+    lat.close()
