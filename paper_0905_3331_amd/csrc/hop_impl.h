@@ -4,6 +4,11 @@
 // that the many template instantiations compile in parallel; hop.hip holds
 // the dispatch.
 //
+// hop_kernel, the lane-per-site form, takes FP64 and FP32 batches, batches of
+// doublets and the rarely used format pairs; hop16_kernel 16-bit spinors on
+// FP16 links; one FP64 or FP32 field or doublet, and a small 16-bit field, run
+// in the split kernels (hop_split.h, hop_split_nd.h; go() draws the line).
+//
 // One output site per lane.  For each of the 8 neighbours the lane loads the
 // neighbour spinor, projects it to two spin components with (1 +- gamma_mu)
 // (Sec. 4.1), multiplies both by the link U(x,mu) or U(x-mu,mu)^+ (each link
@@ -286,34 +291,6 @@ __device__ __forceinline__ void math16(const HopArgs<SP, LK> &a, const Raw16 &d,
             coded_hop<MU, 0>(a, u, d.c[0], d.sc[0], acc);
         else
             coded_hop<MU, 1>(a, u, d.c[1], d.sc[1], acc);
-    }
-}
-
-// The same for FP32 spinors with FP32 two-row links, one direction at a time
-// (two directions at once need about 210 VGPRs and were slower)
-struct Raw32 {
-    su3<float> u[2];        // rows 0 and 1 of the forward and backward link
-    spinor<float> sp[2];    // forward and backward neighbour
-};
-template <int MU, bool NT, class SP, class LK>
-__device__ __forceinline__ void load32(const HopArgs<SP, LK> &a, const SP &in, long h, long hf, long hb, Raw32 &d)
-{
-    a.lk.template load_rows<NT>(a.out_par, MU, h, d.u[0]);
-    in.load(hf, d.sp[0]);
-    a.lk.template load_rows<NT>(a.out_par ^ 1, MU, hb, d.u[1]);
-    in.load(hb, d.sp[1]);
-}
-// the arithmetic of hop_dir for one RHS on loaded data
-template <int MU, class SP, class LK>
-__device__ __forceinline__ void math32(const HopArgs<SP, LK> &a, Raw32 &d, spinor<float> &acc)
-{
-#pragma unroll
-    for (int dir = 0; dir < 2; dir++) {
-        su3_third_row(d.u[dir]);
-        if (dir == 0)
-            plain_hop<MU, 0>(a, d.u[0], d.sp[0], acc);
-        else
-            plain_hop<MU, 1>(a, d.u[1], d.sp[1], acc);
     }
 }
 
@@ -666,7 +643,7 @@ __global__ __launch_bounds__(HOP_BLOCK) void hop_kernel(HopArgs<SP, LK> a)
         auto b2 = [&] { return y == 0 ? h + (g.LY - 1) * sy : h - sy; };
         auto f3 = [&] { return z + 1 == g.LZ ? h - (g.LZ - 1) * sz : h + sz; };
         auto b3 = [&] { return z == 0 ? h + (g.LZ - 1) * sz : h - sz; };
-        // the directions in the order of the sum (K1_ORDER), neighbours by index
+        // the directions in the order of the sum (k1_order), neighbours by index
         constexpr bool XY1 = (SP::coded || __is_same(SP, SpF64)) && !SELF;
         constexpr int D0 = k1_order<XY1>(0), D1 = k1_order<XY1>(1), D2 = k1_order<XY1>(2), D3 = k1_order<XY1>(3);
         auto fn = [&](auto m) -> long {
@@ -704,23 +681,6 @@ __global__ __launch_bounds__(HOP_BLOCK) void hop_kernel(HopArgs<SP, LK> a)
                 load16<D3, NT>(a, in[0], h, fn(I3{}), bn(I3{}), d1);
                 math16<D2>(a, d0, acc[0]);
                 math16<D3>(a, d1, acc[0]);
-            }
-        } else if constexpr (__is_same(SP, SpF32) && __is_same(LK, L32R) && NT && G == 1) {
-            // FP32, single-RHS (or single-doublet) launch: the four loads of a
-            // direction before its arithmetic
-            if (live[0]) {
-                Raw32 d;
-                load32<0, NT>(a, in[0], h, f0(), b0(), d);
-                math32<0>(a, d, acc[0]);
-                if (SB) __builtin_amdgcn_sched_barrier(0);
-                load32<1, NT>(a, in[0], h, f1(), b1(), d);
-                math32<1>(a, d, acc[0]);
-                if (SB) __builtin_amdgcn_sched_barrier(0);
-                load32<2, NT>(a, in[0], h, f2(), b2(), d);
-                math32<2>(a, d, acc[0]);
-                if (SB) __builtin_amdgcn_sched_barrier(0);
-                load32<3, NT>(a, in[0], h, f3(), b3(), d);
-                math32<3>(a, d, acc[0]);
             }
         } else {
             hop_dir<D0, NT>(a, in, live, acc, h, fn(I0{}), bn(I0{}));
@@ -1393,10 +1353,6 @@ inline int rhs_group(const Geom &g, int prec, int n)
     return G < 1 ? 1 : (G > n ? n : G);
 }
 
-// ALL = false: only variant 0 with one RHS per lane is instantiated (rarely
-// used format pairs); MULTI = true adds 2 RHS per lane for batches (the
-// FP32-arithmetic formats; FP64 lanes already use all 256 registers; 4 per
-// lane measured slower than 1 and 2).
 template <class SP, class LK>
 hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &self, const FieldDesc &out,
                         const LinkDesc &lk, const OpParams &op, int epi, int sign, const RhsList &rl, double *partial,
@@ -1408,6 +1364,10 @@ hipError_t launch_split_nd(const Geom &g, int out_par, const FieldDesc &in, cons
                            const RhsList &rl, double *partial, long pstride, const CgScalars *scal, int ord, int nblk,
                            hipStream_t st, const CgFields *cg);
 
+// ALL = false: only variant 0 with one RHS per lane is instantiated (rarely
+// used format pairs); MULTI = true adds 2 RHS per lane for batches (the
+// FP32-arithmetic formats; FP64 lanes already use all 256 registers; 4 per
+// lane measured slower than 1 and 2).
 template <class SP, class LK, bool ALL, bool MULTI>
 hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &self, const FieldDesc &out,
               const LinkDesc &lk, const OpParams &op, int epi, int sign, const RhsList &rl, double *partial,
@@ -1512,10 +1472,13 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
         }
 #define GON(ORD)                                                                \
     do {                                                                        \
-        if (nt)                                                                 \
-            go_nd<SP, LK, true, ORD>(a, s, n, ep, grid, block, tu.lds, st);     \
-        else                                                                    \
-            go_nd<SP, LK, false, ORD>(a, s, n, ep, grid, block, tu.lds, st);    \
+        if constexpr (!ALL || SP::coded) {                                      \
+            if (nt) {                                                           \
+                go_nd<SP, LK, true, ORD>(a, s, n, ep, grid, block, tu.lds, st); \
+                break;                                                          \
+            }                                                                   \
+        }                                                                       \
+        go_nd<SP, LK, false, ORD>(a, s, n, ep, grid, block, tu.lds, st);        \
     } while (0)
         if constexpr (ALL) {
             if (ord == ORD_ZSLAB)
@@ -1581,7 +1544,10 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
             return hipGetLastError();
         }
     }
-    // (a single FP64 or FP32 field went to the split kernel)
+    // (a single FP64 or FP32 field went to the split kernel; a batch measured no
+    // faster there: FP32 K1 of 24 RHS at 24^3x48 617 us here and 627 in a split
+    // kernel that keeps its links in registers over the RHS of a group, which
+    // reads 1.8 GB instead of 2.65 but waits for its barriers)
 #define GOV(ORD, SB)                                                          \
     do {                                                                      \
         if constexpr (SP::coded) {                                            \
