@@ -465,9 +465,10 @@ void tmq_server_destroy(tmq_server *srv);
  * synchronises the device and clears the records.  tmq_kernel_stats returns,
  * for the launches recorded since then, their number, total time in ms, and
  * the algorithmic bytes and flops they move (each input spinor, link and
- * output counted once; 1320 flop per output site per half-sweep; a fused CG
- * epilogue adds its reads of r and p and its read and write of x, a fused
- * residual its read of b).  family is "hop" (all), "hop64", "hop32" or "hop16"
+ * output counted once, a canonical buffer that a half-sweep reads or writes
+ * itself as complex128; 1320 flop per output site per half-sweep; a fused CG
+ * epilogue adds its read of r, whose write is the output, a fused residual
+ * counts its read of b and its write of r).  family is "hop" (all), "hop64", "hop32" or "hop16"
  * (FP16 and BF16 spinor storage), optionally followed by ":pure" (the plain
  * half-sweeps K1 and K2 of eqs. (eo3)/(eo4) only), ":k1", ":k2" or ":fused"
  * (the half-sweeps whose epilogue carries the CG update or the true residual).
@@ -490,8 +491,10 @@ int tmq_stream_copy(int device, size_t bytes, int reps, double *gbps);
  * lexicographic (an eighth of the time-slices per XCD); 1 each XCD walks its
  * own range of z-planes time-slice by time-slice (needs LZ >= 8); 2 as 1 with
  * scheduling barriers between directions; 3 each XCD walks its own range of
- * time-slices z-plane by z-plane (needs T >= 8); 4 as 3 with barriers.  The
- * tuner runs at the first launch of each format on a lattice;
+ * time-slices z-plane by z-plane (needs T >= 8); 4 as 3 with barriers.  A
+ * format whose single fields run with a wavefront per hop (FP64 and FP32, and
+ * 16-bit storage on small lattices) and that is first used on one times the
+ * orders 0, 1 and 3 only and takes no cap.  The tuner runs at the first launch of each format on a lattice;
  * TMQ_HOP_VARIANT=0..4 in the environment forces a variant and
  * TMQ_HOP_CAP=0..5 a cap (single-field and batched launches).  Batched
  * launches list, per (format, power-of-two batch size class), the RHS per

@@ -343,17 +343,46 @@ __device__ __forceinline__ double det_sum(const double *partial, int n, double *
     return block_sum_n<SC_THREADS / 64>(v, sh);  // valid in thread 0
 }
 
+// two such sums over n <= SC_THREADS blocks, their loads together (sh: twice the room)
+__device__ __forceinline__ double2 det_sum2(const double *pa, const double *pb, int n, double *sh)
+{
+    double a = 0.0, b = 0.0;
+    if ((int)threadIdx.x < n) {
+        const double2 *qa = (const double2 *)pa + 2 * threadIdx.x, *qb = (const double2 *)pb + 2 * threadIdx.x;
+        const double2 a0 = qa[0], a1 = qa[1], b0 = qb[0], b1 = qb[1];
+        a += (((0.0 + a0.x) + a0.y) + a1.x) + a1.y;
+        b += (((0.0 + b0.x) + b0.y) + b1.x) + b1.y;
+    }
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if ((threadIdx.x & 63) == 0) {
+        sh[2 * (threadIdx.x >> 6)] = a;
+        sh[2 * (threadIdx.x >> 6) + 1] = b;
+    }
+    __syncthreads();
+    double2 s = make_double2(0.0, 0.0);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < SC_THREADS / 64; i++) {
+            s.x += sh[2 * i];
+            s.y += sh[2 * i + 1];
+        }
+    return s;  // valid in thread 0
+}
+
 __device__ __forceinline__ int finite(double v) { return isfinite(v) ? 1 : 0; }
 
-// one block per RHS of rl (grid x)
+// one block per RHS of rl (grid x); PAP: SC_ALPHA_BETA
+template <bool PAP>
 __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const double *partial, long pstride,
                                                        int nparts, CgScalars *sc, double tol2, int relative,
-                                                       int skip_done, int defer, CgScalars *publish)
+                                                       int skip_done, int defer, CgScalars *publish,
+                                                       const double *pap)
 {
     const int rhs = rl.idx[blockIdx.x];
     // (the scalars are read ahead of the sum and written back whole)
     CgScalars c = sc[rhs], *s = &c;
-    if (op == SC_BETA && s->xpend) {
+    if ((PAP || op == SC_BETA) && s->xpend) {
         s->fresh = 0;
         s->xpend = 0;
     }
@@ -364,8 +393,22 @@ __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const
         }
         return;
     }
-    __shared__ double sh[SC_THREADS / 64];
-    const double sum = det_sum(partial + rhs * pstride, nparts, sh);
+    __shared__ double sh[(PAP ? 2 : 1) * SC_THREADS / 64];
+    double sum;
+    if constexpr (PAP) {
+        const double2 w = det_sum2(pap + rhs * pstride, partial + rhs * pstride, nparts, sh);
+        s->pAp = w.x;
+        s->alpha = s->rr / w.x;
+        if (!finite(s->alpha)) {  // (the half-sweep did nothing)
+            s->nan = 1, s->done = 1;
+            op = -1;
+        } else {
+            op = SC_BETA;
+        }
+        sum = w.y;
+    } else {
+        sum = det_sum(partial + rhs * pstride, nparts, sh);
+    }
     if (threadIdx.x != 0) return;
     switch (op) {
     case SC_INIT:  // sum = ||b||^2 = ||r_0||^2 (x_0 = 0)
@@ -552,11 +595,18 @@ hipError_t launch_join(const double2 *src, const FieldDesc &b, const FieldDesc &
 
 hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long pstride, int nparts,
                          CgScalars *s, double tol2, int relative, bool skip_done, bool defer,
-                         CgScalars *publish, hipStream_t st)
+                         CgScalars *publish, hipStream_t st, const double *pap)
 {
     if (rl.n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scalar, dim3(rl.n), dim3(SC_THREADS), 0, st, op, rl, partial, pstride, nparts, s, tol2,
-                       relative, skip_done ? 1 : 0, defer ? 1 : 0, publish);
+    if (op == SC_ALPHA_BETA && (!pap || nparts > SC_THREADS)) return hipErrorInvalidValue;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(rl.n), dim3(SC_THREADS), 0, st, op, rl, partial, pstride, nparts, s, tol2,
+                           relative, skip_done ? 1 : 0, defer ? 1 : 0, publish, pap);
+    };
+    if (op == SC_ALPHA_BETA)
+        go(k_scalar<true>);
+    else
+        go(k_scalar<false>);
     return hipGetLastError();
 }
 

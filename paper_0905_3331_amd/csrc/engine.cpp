@@ -286,15 +286,19 @@ static int enqueue_body(Engine *E, const std::vector<int> &all, const std::vecto
     } else if (al.n > 0) {
         // t = Qhat^- p, <p, A p> = |t|^2 ; A p = Qhat^+ t
         TMQ_TRY(apply_Qhat(L, E->op, -1, E->ps, E->tos, E->tes, E->lks, al, E->partial[0], S, st));
-        TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, L->hop_blocks_last, S, 0, 0, true, false,
-                              nullptr, st));
+        const int np = L->hop_blocks_last;
+        // one field of a small lattice: alpha from the partials in the next half-sweep but one
+        const bool own = al.n == 1 && !E->nd && hop_sums_alpha(L->g, E->ps.prec, E->lks.fmt, np);
+        if (!own)
+            TMQ_HIP(launch_scalar(SC_ALPHA, al, E->partial[0], L->pstride, np, S, 0, 0, true, false, nullptr, st));
         // A p = Qhat^+ t fused with r -= alpha A p ; |r|^2 ; then beta (x_s += alpha p
         // goes with the update of p)
         CgFields cg;
         cg.r = E->rs;
+        if (own) cg.pap = E->partial[0], cg.npap = np;
         TMQ_TRY(apply_Qhat_cg(L, E->op, E->tos, E->tes, E->lks, al, cg, E->partial[1], S, st));
-        TMQ_HIP(launch_scalar(SC_BETA, al, E->partial[1], L->pstride, L->hop_blocks_last, S, 0, 0, true, true, pub,
-                              st));
+        TMQ_HIP(launch_scalar(own ? SC_ALPHA_BETA : SC_BETA, al, E->partial[1], L->pstride, np, S, 0, 0, true, true,
+                              pub, st, own ? E->partial[0] : nullptr));
     }
     return TMQ_OK;
 }

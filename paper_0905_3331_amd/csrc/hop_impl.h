@@ -1414,6 +1414,7 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
                                         hop_order(variant), hop_grid_variant(g, variant), st, cg);
         }
     }
+    if (cg && cg->pap) return hipErrorInvalidValue;  // (hop_sums_alpha: the split kernel alone)
     // (other launches: the 16-bit kernel alone writes a canonical output, of K2)
     if (in.layout || self.layout) return hipErrorInvalidValue;
     if (ep == EP_STORE && out.layout) {

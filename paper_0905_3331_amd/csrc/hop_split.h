@@ -36,6 +36,11 @@ constexpr int SPLIT_THREADS = 512;  // eight wavefronts
 
 // which operands are canonical complex128 buffers: the input, the own-site
 // field, the output; and whether these hold the whole lattice
+// EP_CG with alpha formed from the partials of <p, A p> (SplitArgs::pap; an
+// instantiation of its own: the registers it takes cost the others 0.7 % of an
+// FP64 solve at 24^3x48)
+constexpr int EP_CG_OWN = 4;
+
 enum SplitCan { CAN_IN = 1, CAN_SELF = 2, CAN_OUT = 4, CAN_FULL = 8 };
 
 template <class SP, class LK>
@@ -53,6 +58,8 @@ struct SplitArgs {
     const CgScalars *scal;
     float one;  // 1.0, opaque to the compiler (see code_lo in fields.h)
     SP cg_r;      // fused epilogues: r (CG update) or b (true residual)
+    const double *pap;  // EP_CG_OWN: the partials of <p, A p> of npap blocks
+    int npap;
     AnyView res;  // the true residual, in its format
     const double2 *cin, *cself;  // canonical operands (SplitCan)
     double2 *cout;
@@ -253,6 +260,7 @@ struct SplitShared {
     R2 sh[8][6][SPLIT_SITES];                                // the half spinors of the hops
     float shs[SP::coded ? 8 : 1][SPLIT_SITES];               // their factors (16-bit spinors)
     float shm[SP::coded ? SplitIo<SP>::NU : 1][SPLIT_SITES];  // largest magnitude of each unit's components
+    double pap[SPLIT_THREADS / 64];                          // <p, A p>, the sums of the wavefronts
 };
 
 // wavefront W's work
@@ -267,9 +275,19 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
     constexpr int MU = k1_order<XY1>(W >> 1);
     constexpr bool BACK = W & 1;
     constexpr bool UNIT = W < NU;
+    constexpr bool CG = EP == EP_CG || EP == EP_CG_OWN;
     const Geom &g = a.g;
     const int lane = p.lane;
     const uint32_t h = p.h;
+    // the partial sums of <p, A p> of block 64 W + lane, summed as the scalar kernels do
+    double2 pa = make_double2(0.0, 0.0), pb = pa;
+    if constexpr (EP == EP_CG_OWN) {
+        const int k = W * 64 + lane;
+        if (k < a.npap) {
+            pa = ((const double2 *)a.pap)[2 * k];
+            pb = ((const double2 *)a.pap)[2 * k + 1];
+        }
+    }
     // what the unit needs of its own site, asked for with the hop's operands
     cx<R> sf[UC], rr[UC];
     if (p.active) {
@@ -311,7 +329,7 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
             } else if (SELF) {
                 IO::load_unit(a.self, h, W, sf);
             }
-            if (EP == EP_CG || EP == EP_RES) IO::load_unit(a.cg_r, h, W, rr);
+            if (CG || EP == EP_RES) IO::load_unit(a.cg_r, h, W, rr);
         }
         half<R> hv;
         float sc = 0.f;
@@ -324,7 +342,20 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
         }
         if constexpr (SP::coded) S.shs[W][lane] = sc;
     }
+    if constexpr (EP == EP_CG_OWN) {
+        const double s = wave_sum((((0.0 + pa.x) + pa.y) + pb.x) + pb.y);
+        if (lane == 0) S.pap[W] = s;
+    }
     __syncthreads();
+    R ar = R(0);  // alpha
+    if constexpr (EP == EP_CG_OWN) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < SPLIT_THREADS / 64; i++) s += S.pap[i];
+        const double al = a.scal[a.rhs].rr / s;
+        if (!isfinite(al)) return;  // (all wavefronts: the scalar kernel ends the solve)
+        ar = (R)al;
+    }
 
     // the units: sum, site terms, update
     cx<R> o[UC];
@@ -360,9 +391,9 @@ __device__ __forceinline__ void split_role(const SplitArgs<SP, LK> &a, SplitShar
                 }
                 o[N] = fma(A, sf[N], B * acc);
             }
-            if constexpr (EP == EP_CG) {
+            if constexpr (CG) {
                 // r -= alpha (A p)
-                const R ar = (R)a.scal[a.rhs].alpha;
+                if constexpr (EP == EP_CG) ar = (R)a.scal[a.rhs].alpha;
                 o[N].re = fmad(-ar, o[N].re, rr[N].re);
                 o[N].im = fmad(-ar, o[N].im, rr[N].im);
             }
@@ -548,6 +579,9 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
         a.cg_r = field(ep == EP_CG ? cg->r : cg->b);
         if (ep == EP_RES) a.res = make_any(field_rhs(cg->r, r));
     }
+    a.pap = ep == EP_CG && cg->pap ? cg->pap + r * pstride : nullptr;
+    a.npap = a.pap ? cg->npap : 0;
+    if (a.npap > SPLIT_THREADS) return hipErrorInvalidValue;
     // canonical operands: the input with the own-site field (if any), the output
     const bool fused = ep != EP_STORE, sl = self.data != nullptr;
     const int full = in.layout == LAY_CANONICAL_FULL || out.layout == LAY_CANONICAL_FULL ? CAN_FULL : 0;
@@ -591,7 +625,9 @@ hipError_t launch_split(const Geom &g, int out_par, const FieldDesc &in, const F
 #undef SPLIT_CAN
         return hipErrorInvalidValue;
     }
-    if (ep == EP_CG)
+    if (a.pap)
+        hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, true, EP_CG_OWN>), grid, block, 0, st, a);
+    else if (ep == EP_CG)
         hipLaunchKernelGGL((hop_split_kernel<SP, LK, true, true, EP_CG>), grid, block, 0, st, a);
     else if (ep == EP_RES) {
         if constexpr (__is_same(SP, SpF64))

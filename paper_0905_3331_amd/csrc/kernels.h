@@ -127,6 +127,10 @@ enum HopEpi { EPI_K1 = 0, EPI_K2 = 1, EPI_FULL = 2, EPI_K2_CG = 3, EPI_K2_RES = 
 // EPI_K2_CG), and for EPI_K2_RES b in the hop's format.
 struct CgFields {
     FieldDesc r, b;
+    // EPI_K2_CG of a launch of hop_sums_alpha: partial sums of <p, A p> of npap
+    // blocks, from which the half-sweep forms alpha itself (else scal's)
+    const double *pap = nullptr;
+    int npap = 0;
 };
 
 // Device scalars of a CG solve (one struct per right-hand side).
@@ -193,6 +197,17 @@ inline bool hop_takes_split(const Geom &g, int prec, int link_fmt)
     if (prec == P64) return true;
     if (prec == P32) return link_fmt == LK32R;
     return link_fmt == LK16R && g.vh <= 49152;
+}
+// whether the CG half-sweep of a single field sums the nparts blocks' partials
+// of <p, A p> itself (SC_ALPHA_BETA follows it): a launch and the wait between
+// two kernels less per iteration, for as many reads of the partials as there are
+// blocks.  A wavefront takes 64 of them, so a block's eight take 512.  Solves
+// with a launch of its own -> here, us: FP32 8^3x16 (16 blocks) 1120 -> 1058,
+// 16^3x32 (256) 2217 -> 2160; FP64 1344 -> 1296, 3216 -> 3203; with 512 blocks
+// (16^3x64) FP32 3501 -> 3483, FP64 the same, so the line is drawn there.
+inline bool hop_sums_alpha(const Geom &g, int prec, int link_fmt, int nparts)
+{
+    return hop_takes_split(g, prec, link_fmt) && nparts <= 512;
 }
 // whether a launch of 16-bit spinors on FP16 two-row links runs in the 16-bit
 // kernel (hop16_kernel): 32-bit offsets (V/2 < 2^26) and a boundary phase in
@@ -278,7 +293,8 @@ enum ScalarOp {
     SC_INIT = 0,     // bb = rr = sum ; target = tol2 * (relative ? bb : 1) ; counters cleared
     SC_ALPHA = 1,    // pAp = sum ; alpha = rr / pAp
     SC_BETA = 2,     // rr_prev = rr ; rr = sum ; beta = rr / rr_prev ; iter++ ; done = rr < target
-    SC_RELIABLE = 3  // rr = sum (true residual) ; beta = rr / rr_prev ; done = rr < target
+    SC_RELIABLE = 3,  // rr = sum (true residual) ; beta = rr / rr_prev ; done = rr < target
+    SC_ALPHA_BETA = 4  // SC_ALPHA of the partials at pap, then SC_BETA (nparts at most 1024)
 };
 // defer: the solve leaves x += alpha p to launch_xpay: SC_INIT and SC_RELIABLE
 // set fresh to it (and xpend to 0), SC_BETA xpend (0 for a skipped RHS; an
@@ -287,7 +303,7 @@ enum ScalarOp {
 // (host-mapped memory), also when the block is skipped.
 hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long pstride, int nparts,
                          CgScalars *scal, double tol2, int relative, bool skip_done, bool defer,
-                         CgScalars *publish, hipStream_t st);
+                         CgScalars *publish, hipStream_t st, const double *pap = nullptr);
 // out[i] = sum of the partials of nparts blocks of RHS rl.idx[i], in the order of the scalar kernels
 hipError_t launch_sums(const RhsList &rl, const double *partial, long pstride, int nparts, double *out, hipStream_t st);
 // out[0] = deterministic maximum of partial[0..n)

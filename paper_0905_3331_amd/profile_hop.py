@@ -40,7 +40,8 @@ if ROOT not in sys.path:
 
 # sources that determine the hop kernels' memory traffic
 KERNEL_SOURCES = ("hop_impl.h", "hop.hip", "hop_f64.hip", "hop_f32.hip", "hop_f16.hip", "hop_b16.hip",
-                  "hop16_f16.hip", "hop16_b16.hip",
+                  "hop16_f16.hip", "hop16_b16.hip", "hop_split.h", "hop_split_nd.h",
+                  "hop_split_f64.hip", "hop_split_f32.hip", "hop_split_f16.hip", "hop_split_b16.hip",
                   "fields.h", "spin.h", "views.h", "kernels.h", "devutil.h", "fastdiv.h")
 
 
@@ -62,9 +63,13 @@ def kernel_hash() -> str:
     return h.hexdigest()[:16]
 
 
+HOP_KERNELS = ("hop_kernel<", "hop16_kernel<", "hop_split_kernel<", "hop_split_nd_kernel<")
+
+
 def is_hop(name: str) -> bool:
-    """A hop half-sweep kernel: the general hop_kernel or the 16-bit hop16_kernel."""
-    return "hop_kernel<" in name or "hop16_kernel<" in name
+    """A hop half-sweep kernel: the general hop_kernel, the 16-bit hop16_kernel
+    or the split kernels of one field or doublet."""
+    return any(k in name for k in HOP_KERNELS)
 
 
 def hop_family(name: str):
@@ -82,11 +87,12 @@ def hop_family(name: str):
 def hop_template_args(name: str):
     """Template arguments of a hop kernel instantiation, as text, in order:
     hop_kernel: spinor format, link format, SELF, NORM, NT, ORD, SB, G, EP, ND;
-    hop16_kernel: spinor format, SELF, NORM, ORD, SB, EP, ND, PM, K2F, BATCH."""
-    key = "hop16_kernel<" if "hop16_kernel<" in name else "hop_kernel<"
-    i = name.find(key)
-    if i < 0:
+    hop16_kernel: spinor format, SELF, NORM, ORD, SB, EP, ND, PM, K2F, BATCH;
+    hop_split_kernel, hop_split_nd_kernel: spinor format, link format, SELF, NORM, EP."""
+    key = next((k for k in HOP_KERNELS if k in name), None)
+    if key is None:
         return None
+    i = name.find(key)
     depth, cur, args = 0, "", []
     for ch in name[i + len(key):]:
         if ch == "<":
@@ -111,6 +117,8 @@ def hop_part(name: str):
     a = hop_template_args(name)
     if a and "hop16_kernel<" in name and len(a) >= 8:
         self_, ep = a[1] == "true", a[5]
+    elif a and "hop_split" in name and len(a) >= 5:
+        self_, ep = a[2] == "true", a[4]
     elif a and len(a) >= 10:
         self_, ep = a[2] == "true", a[8]
     else:

@@ -191,3 +191,28 @@ def test_solve_M_batch_passes(tmq, dims, sign):  # noqa: F811
             assert i.status == 0 and res <= tol * (1 + 1e-6), (tol, res)
             assert abs(res - i.true_rel_residual) <= 1e-3 * res + 1e-16
     lat.close()
+
+
+@pytest.mark.parametrize("kappa", [0.1632, 1e160], ids=["", "overflow"])
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (16, 16, 16, 64), (16, 16, 16, 66)], ids=lambda d: "x".join(map(str, d)))
+def test_alpha_in_the_half_sweep(tmq, dims, kappa):  # noqa: F811
+    """One field forms alpha in its CG half-sweep up to 512 blocks (the second
+    size has them, the third more), a batch in the scalar kernel: the same
+    iterates bit for bit, and the same end where <p, A p> overflows."""
+    U = synth.random_gauge((4, 4, 4, 4), seed=304)
+    U = np.tile(U, tuple(-(-d // 4) for d in dims) + (1, 1, 1))[tuple(slice(d) for d in dims)]
+    lat = tmq.Lattice(dims)
+    lat.load_gauge(dev(np.ascontiguousarray(U)))
+    n = int(np.prod(dims)) // 2
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(71)
+    bs = [torch.view_as_complex(torch.randn(n, 4, 3, 2, dtype=torch.float64, device="cuda", generator=gen)) for _ in "ab"]
+    p = tmq.params(kappa, 0.004, THETA)
+    for prec in ("fp64", "fp32"):
+        o = tmq.solver_opts(tol=1e-12, sloppy=prec, sloppy_link="fp32", max_iter=6)
+        xs, infos = lat.solve_batch([p, p], bs, o, check=False)
+        x1, i1 = lat.solve(p, bs[0], o, check=False)
+        assert (i1.status, i1.iters) == (infos[0].status, infos[0].iters)
+        assert (i1.iters == 6) == (kappa < 1)
+        assert torch.equal(torch.view_as_real(x1).nan_to_num(7.0), torch.view_as_real(xs[0]).nan_to_num(7.0))
+    lat.close()

@@ -183,3 +183,13 @@ def test_kernel_hash_ignores_comments():
     assert profile_hop.code_text(src.replace("one", "two")) == profile_hop.code_text(src)
     assert profile_hop.code_text(src.replace("2;", "3;")) != profile_hop.code_text(src)
 
+
+def test_split_kernels_are_hop_kernels():
+    """The split half-sweeps count in the family of their spinors, by part."""
+    sp = "void tmq::hop_split_kernel<tmq::SpF64, tmq::L64R, %s, %s, %d, %d>(tmq::SplitArgs<tmq::SpF64, tmq::L64R>)"
+    nd = "void tmq::hop_split_nd_kernel<tmq::SpF32, tmq::L32R, %s, %s, %d>(tmq::SplitNdArgs<tmq::SpF32, tmq::L32R>)"
+    h16 = "void tmq::hop_split_kernel<tmq::Sp16<false>, tmq::L16R, true, false, 0, 4>(args)"
+    k1, k2, cg = sp % ("false", "false", 0, 1), sp % ("true", "true", 0, 0), sp % ("true", "true", 1, 0)
+    assert [profile_hop.hop_part(k) for k in (k1, k2, cg, h16)] == ["k1", "k2", "fused", "k2"]
+    assert [profile_hop.hop_part(nd % a) for a in (("false", "false", 0), ("true", "true", 2))] == ["k1", "fused"]
+    assert [profile_hop.hop_family(k) for k in (k1, nd % ("true", "false", 0), h16)] == ["hop64", "hop32", "hop16"]
