@@ -141,7 +141,7 @@ def traffic_markdown(res, title, algorithmic=None):
     half-sweep averages, then every instantiation.  algorithmic: optional
     {family or part: algorithmic bytes per launch} printed beside them."""
     algorithmic = algorithmic or {}
-    lines = [f"# {title}", "", "Commands (GPU box, repo root; one pass per counter):", "", "    " + res["command"], "",
+    lines = [f"# {title}", "", "Commands (repo root, one MI355X; one pass per counter):", "", "    " + res["command"], "",
              f"Calibration: the plain copy kernel (k_stream_copy) reads and writes {res['copy_bytes']} bytes per launch; "
              f"HBM read bytes = FETCH_SIZE x 1024 x {res['fetch_scale']:.4f}, write bytes = WRITE_SIZE x 1024 x "
              f"{res['write_scale']:.4f}.", "",
@@ -325,7 +325,7 @@ def summarize_batch_sweep(fetch_csv, sweep_json, cmd, out):
         if ci >= 0 and hop_family(k) == "hop32" and part:
             acc[ci][part].append(v * 1024.0 * scale)
     lines = ["# Batched FP32 half-sweeps, 48 right-hand sides at 24^3x48: block order x RHS group", "",
-             "Commands (GPU box; the sweep, then one counter pass over the same sweep):", "", "    " + cmd, "",
+             "Commands (one MI355X; the sweep, then one counter pass over the same sweep):", "", "    " + cmd, "",
              f"Kernel sources hash: {kernel_hash()}.  Reads scaled by the 1 MiB marker copies (x {scale:.4f}); "
              "times from events in a run without the profiler.", "",
              "| block order | RHS group | K1 us | K2 us | fused K2 us | K1 HBM read MB | K1 algorithmic read MB | ratio |",
