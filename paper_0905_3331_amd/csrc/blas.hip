@@ -454,6 +454,17 @@ __global__ __launch_bounds__(SC_THREADS) void k_scalar(int op, RhsList rl, const
     if (publish) publish[rhs] = c;
 }
 
+// the pending update of x has been applied: x holds it (one lane per RHS)
+__global__ __launch_bounds__(MAX_RHS) void k_x_applied(RhsList rl, CgScalars *sc)
+{
+    if ((int)threadIdx.x >= rl.n) return;
+    CgScalars &s = sc[rl.idx[threadIdx.x]];
+    if (s.xpend) {
+        s.xpend = 0;
+        s.fresh = 0;
+    }
+}
+
 // out[i] = the sum of RHS rl.idx[i]
 __global__ __launch_bounds__(SC_THREADS) void k_sums(RhsList rl, const double *partial, long pstride, int nparts,
                                                      double *out)
@@ -607,6 +618,13 @@ hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long 
         go(k_scalar<true>);
     else
         go(k_scalar<false>);
+    return hipGetLastError();
+}
+
+hipError_t launch_x_applied(const RhsList &rl, CgScalars *s, hipStream_t st)
+{
+    if (rl.n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_x_applied, dim3(1), dim3(MAX_RHS), 0, st, rl, s);
     return hipGetLastError();
 }
 

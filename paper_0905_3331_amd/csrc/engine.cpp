@@ -409,7 +409,7 @@ int engine_end_step(Engine *E, std::vector<int> *finished)
     const int cur = (int)(s % Lattice::RING);
     CgScalars *pub = E->ring_dev + (size_t)cur * E->cap;
     const std::vector<int> in_body = body_slots(E);
-    std::vector<int> ru;
+    std::vector<int> ru, ended;
     if (s > 0) {
         const int prev_slot = (int)((s - 1) % Lattice::RING);
         TMQ_HIP(hipEventSynchronize(E->step_ev[prev_slot]));
@@ -426,10 +426,12 @@ int engine_end_step(Engine *E, std::vector<int> *finished)
                 continue;
             }
             if (k >= sl.max_iter) {  // no more bodies: end on a true residual
-                if (pv.last_true)
+                if (pv.last_true) {
                     finish(sl, pv, r, finished);
-                else
+                } else {
                     ru.push_back(r);
+                    ended.push_back(r);
+                }
                 continue;
             }
             if (pv.done) {  // iterated residual met the target: check the true one
@@ -442,7 +444,10 @@ int engine_end_step(Engine *E, std::vector<int> *finished)
             if (E->switching && !sl.switched && pv.rr < sl.tol * (sl.relative ? pv.bb : 1.0)) sl.switched = true;
         }
     }
-    // reliable updates after this step's body publish to the same ring entry
+    // reliable updates after this step's body publish to the same ring entry;
+    // a slot without a body in this step has no update of x pending: the last
+    // step's launch_xpay applied it, which its scalars do not say yet
+    TMQ_HIP(launch_x_applied(list_of(ended), E->scal, E->st));
     TMQ_TRY(reliable_update(E, list_of(ru), pub));
     if (!in_body.empty()) TMQ_HIP(launch_xpay(E->rs, E->ps, E->xs, list_of(in_body), E->scal, true, false, E->st));
     TMQ_HIP(hipEventRecord(E->step_ev[cur], E->st));

@@ -304,6 +304,9 @@ enum ScalarOp {
 hipError_t launch_scalar(int op, const RhsList &rl, const double *partial, long pstride, int nparts,
                          CgScalars *scal, double tol2, int relative, bool skip_done, bool defer,
                          CgScalars *publish, hipStream_t st, const double *pap = nullptr);
+// xpend = 0 after launch_xpay has applied the update, and x not fresh: for RHS
+// that go on without the iteration whose SC_BETA would do this
+hipError_t launch_x_applied(const RhsList &rl, CgScalars *scal, hipStream_t st);
 // out[i] = sum of the partials of nparts blocks of RHS rl.idx[i], in the order of the scalar kernels
 hipError_t launch_sums(const RhsList &rl, const double *partial, long pstride, int nparts, double *out, hipStream_t st);
 // out[0] = deterministic maximum of partial[0..n)
