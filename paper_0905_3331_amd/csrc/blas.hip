@@ -12,8 +12,6 @@
 
 namespace tmq {
 
-int blas_grid(long n) { return (int)((n + BLAS_BLOCK - 1) / BLAS_BLOCK); }
-
 RhsList rhs_all(int n)
 {
     RhsList l;

@@ -1,42 +1,9 @@
 // hop.hip -- dispatch of the hopping half-sweep to the per-format translation
-// units, the variant table and grid sizes.
+// units.
 #include "devutil.h"
 #include "views.h"
 
 namespace tmq {
-
-int hop_grid(long n)
-{
-    long g = (n + HOP_BLOCK - 1) / HOP_BLOCK;
-    g = (g + 7) / 8 * 8;  // a multiple of the XCD count for the remap
-    return (int)g;
-}
-
-
-bool hop_variant_valid(const Geom &g, int v)
-{
-    if (v < 0 || v >= HOP_VARIANTS) return false;
-    if (hop_order(v) == ORD_ZSLAB) return g.LZ >= 8;
-    if (hop_order(v) == ORD_TSLAB) return g.T >= 8;
-    return true;
-}
-
-int hop_grid_variant(const Geom &g, int v, int lanes_per_site)
-{
-    const long L = lanes_per_site;
-    if (!hop_variant_valid(g, v) || hop_order(v) == ORD_PLAIN) return hop_grid(L * g.vh);
-    const long plane = (long)g.LY * g.XH;
-    long per_xcd;
-    if (hop_order(v) == ORD_ZSLAB) {
-        const long zc = g.LZ / 8 + (g.LZ % 8 ? 1 : 0);
-        per_xcd = (L * g.T * zc * plane + HOP_BLOCK - 1) / HOP_BLOCK;
-    } else {
-        const long tc = g.T / 8 + (g.T % 8 ? 1 : 0);
-        per_xcd = (L * g.LZ * tc * plane + HOP_BLOCK - 1) / HOP_BLOCK;
-    }
-    return (int)(8 * per_xcd);
-}
-
 
 bool hop_all_variants(int prec, int link_fmt)
 {

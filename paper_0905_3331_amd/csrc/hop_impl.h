@@ -1407,11 +1407,13 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
     if (ALL != hop_all_variants(in.prec, lk.fmt)) return hipErrorInvalidValue;  // tables out of step
     int variant = tu.variant;
     if (!ALL || !hop_variant_valid(g, variant)) variant = 0;
+    const int nblk = hop_grid_variant(g, variant, op.nd ? hop_nd_lanes(g, in.prec, lk.fmt, op) : 1);
+    if (partial && (long)PARTS * nblk > pstride) return hipErrorInvalidValue;
     if constexpr (ALL) {
         if (rl.n == 1 && !op.nd && hop_takes_split(g, in.prec, lk.fmt)) {
             if (epi != EPI_K1 && !self.data) return hipErrorInvalidValue;
             return launch_split<SP, LK>(g, out_par, in, self, out, lk, op, epi, sign, rl, partial, pstride, scal,
-                                        hop_order(variant), hop_grid_variant(g, variant), st, cg);
+                                        hop_order(variant), nblk, st, cg);
         }
     }
     if (cg && cg->pap) return hipErrorInvalidValue;  // (hop_sums_alpha: the split kernel alone)
@@ -1451,10 +1453,10 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
             // one FP64 or FP32 doublet: the split kernel, with the sums of the lane pairs
             if (rl.n == 2)
                 return launch_split_nd<SP, LK>(g, out_par, in, self, out, lk, op, epi, sign, rl, partial, pstride, scal,
-                                               hop_order(variant), hop_grid_variant(g, variant, 2), st, cg);
+                                               hop_order(variant), nblk, st, cg);
         }
         const int lanes = hop_nd_lanes(g, in.prec, lk.fmt, op);  // per doublet site
-        a.nblk = hop_grid_variant(g, variant, lanes);
+        a.nblk = nblk;
         const int ntup = rl.n / 2;
         const int grp = tu.group > 0 ? tu.group : rhs_group(g, in.prec, rl.n);
         a.group = (grp + 1) / 2;
@@ -1497,7 +1499,7 @@ hipError_t go(const Geom &g, int out_par, const FieldDesc &in, const FieldDesc &
     int G = MULTI && ALL && rl.n > 1 ? tu.rpl : 1;
     if (G != 2) G = 1;
     const int ntup = (rl.n + G - 1) / G;
-    a.nblk = hop_grid_variant(g, variant);
+    a.nblk = nblk;
     const int grp = tu.group > 0 ? tu.group : rhs_group(g, in.prec, rl.n);  // in RHS
     a.group = (grp + G - 1) / G;
     if (a.group > ntup) a.group = ntup;

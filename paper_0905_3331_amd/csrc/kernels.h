@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "fastdiv.h"
+#include "hop_grid.h"
 
 namespace tmq {
 
@@ -25,14 +26,6 @@ enum LinkFmt { LK64F = 0, LK64R = 1, LK32R = 2, LK16R = 3, LK32F = 4 };
 constexpr int N_LINK_FMT = 8;  // stride of the (spinor precision, link format) tuning keys
 
 constexpr int MAX_RHS = 64;
-
-// Lattice geometry.  Extents (T, LZ, LY, LX) all even; V/2 sites per parity,
-// eo index h = site >> 1 with site = ((t*LZ + z)*LY + y)*LX + x.
-struct Geom {
-    int T, LZ, LY, LX;
-    int XH;   // LX / 2
-    long vh;  // V / 2
-};
 
 // How a field is laid out: the device layout of its precision, or a caller's
 // canonical complex128 buffer that a half-sweep reads or writes itself
@@ -151,29 +144,9 @@ struct CgScalars {
     int fresh;       // 1: the solution (correction) holds nothing yet and counts as zero
 };
 
-constexpr int HOP_BLOCK = 256;
-constexpr int BLAS_BLOCK = 256;
-// partial sums that a block of 256 lanes leaves, one per wavefront (the split
-// half-sweep's blocks hold a wavefront's sites, so a sum does not depend on the kernel)
-constexpr int PARTS = 4;
-
-int hop_grid(long n);
-int blas_grid(long n);
-
-// hop kernel variants (see hop.hip): 0 plain order, 1 z-slabs per XCD, 2
-// z-slabs + scheduling barriers, 3 t-slabs per XCD, 4 t-slabs + barriers.
-// z-slabs need LZ >= 8, t-slabs T >= 8.  Links are loaded non-temporally in
-// single-RHS launches and cached in batched ones.
-enum HopOrder { ORD_PLAIN = 0, ORD_ZSLAB = 1, ORD_TSLAB = 2 };
-constexpr int HOP_VARIANTS = 5;
-inline int hop_order(int v) { return v == 0 ? ORD_PLAIN : v <= 2 ? ORD_ZSLAB : ORD_TSLAB; }
-bool hop_variant_valid(const Geom &g, int v);
 // whether the (spinor precision, link format) pairing has every variant; the
 // others always run variant 0 whatever HopTune asks for
 bool hop_all_variants(int prec, int link_fmt);
-// blocks of HOP_BLOCK sites per RHS of variant v (PARTS partial sums each with a norm);
-// lanes_per_site = 2 for doublets in the general kernel (a lane pair per site)
-int hop_grid_variant(const Geom &g, int v, int lanes_per_site = 1);
 
 // bit mu set when the boundary phase of direction mu is not 1
 inline int hop_phase_mask(const OpParams &op)

@@ -180,8 +180,8 @@ int lattice_create(const int dims[4], int device, Lattice **out)
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
         L->lds_per_block = lds;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeWallClockRate, device) == hipSuccess && lds > 0) L->wall_khz = lds;
-    // per RHS: at least as many partials as any hop variant or vector kernel writes
-    L->pstride = PARTS * (hop_grid(2 * L->g.vh) + 64);
+    // per RHS: at least as many partials as any half-sweep or vector kernel writes
+    L->pstride = hop_partials(L->g);
     for (auto &p : L->partial)
         if (hipMalloc((void **)&p, sizeof(double) * L->pstride * MAX_RHS) != hipSuccess)
             return fail(TMQ_ENOMEM, "partials");
