@@ -23,11 +23,12 @@ size_t engine_slot_bytes(long vh, int sloppy, int mode, bool nd)
     // switch mode: b, x, r, t_e, t_o, p, A p in FP64 and p, A p, t_e, t_o reduced
     if (mode == TMQ_MODE_SWITCH)
         return 7 * field_bytes(P64, vh) + (sloppy == P64 ? 0 : 4 * field_bytes(sloppy, vh));
-    // FP64: b, x, r, t_e, t_o, p ; mixed: b, x, r, t_e, t_o in FP64, four inner
+    // FP64: b, x, r, t_e, t_o, p ; mixed: b, x, t_e, t_o in FP64, four inner
     // vectors (r, p, t_e, t_o) and the FP32 x_s (A p never reaches memory: the
-    // CG update is fused into the half-sweep that forms it)
+    // CG update is fused into the half-sweep that forms it; the FP64 residual of
+    // a reliable update is stored as the inner r)
     if (sloppy == P64) return 6 * field_bytes(P64, vh);
-    return 5 * field_bytes(P64, vh) + 4 * field_bytes(sloppy, vh) + field_bytes(P32, vh);
+    return 4 * field_bytes(P64, vh) + 4 * field_bytes(sloppy, vh) + field_bytes(P32, vh);
 }
 
 size_t engine_bytes(const Lattice *L, int sloppy, int cap, int mode, bool nd)
@@ -95,8 +96,9 @@ int engine_create(Lattice *L, int sloppy, int sloppy_link, int mode, int cap, hi
         return TMQ_OK;
     };
     int s = TMQ_OK;
-    for (FieldDesc *d : {&E->b, &E->x, &E->r64, &E->te64, &E->to64})
+    for (FieldDesc *d : {&E->b, &E->x, &E->te64, &E->to64})
         if ((s = field(P64, d)) != TMQ_OK) return fail(s);
+    if (!E->mixed && (s = field(P64, &E->r64)) != TMQ_OK) return fail(s);
     E->lk64 = lattice_links(L, link_fmt_for(L, P64, P64));
     if (E->mixed) {
         E->lks = lattice_links(L, link_fmt_for(L, sloppy, sloppy_link));

@@ -50,7 +50,7 @@ struct Engine {
     long n = 0;             // sites of a slot's fields: V/2, or 2 V/2 for doublets
 
     std::vector<Field> fields;
-    FieldDesc b, x, r64, te64, to64, rs, ps, tes, tos, xs;
+    FieldDesc b, x, r64, te64, to64, rs, ps, tes, tos, xs;  // (r64: none in mixed precision)
     FieldDesc ap64, pss, apss;  // switch mode: FP64 A p, reduced-precision p and A p
     LinkDesc lk64{}, lks{};
     OpParams op{};
