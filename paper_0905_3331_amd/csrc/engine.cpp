@@ -33,8 +33,8 @@ size_t engine_slot_bytes(long vh, int sloppy, int mode, bool nd)
 
 size_t engine_bytes(const Lattice *L, int sloppy, int cap, int mode, bool nd)
 {
-    return (size_t)cap * engine_slot_bytes(L->g.vh, sloppy, mode, nd) + (size_t)cap * 3 * (L->pstride / PARTS) * sizeof(double) +
-           (size_t)cap * sizeof(CgScalars);
+    return (size_t)cap * (engine_slot_bytes(L->g.vh, sloppy, mode, nd) + 3 * L->pstride * sizeof(double) +
+                          sizeof(CgScalars));
 }
 
 double engine_default_delta(int sloppy, int sloppy_link)

@@ -58,7 +58,7 @@ inline int hop_grid_variant(const Geom &g, int v, int lanes_per_site = 1)
 // divide, a slab order has more blocks than the plain one (1.6 times for 10).
 inline long hop_partials(const Geom &g)
 {
-    long n = hop_grid(2 * g.vh) + 64;
+    long n = blas_grid(2 * g.vh);
     for (int v = 0; v < HOP_VARIANTS; v++)
         for (int lanes = 1; lanes <= 2; lanes++) {
             const long k = hop_grid_variant(g, v, lanes);

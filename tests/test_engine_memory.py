@@ -54,3 +54,30 @@ def test_memory_of_a_batch(sloppy):
     want = (n - 1) * slot_fields(sloppy, "reliable") * vh
     assert abs(took - want) < n * 192 * vh // 2, (took, want)
     lat.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("sloppy", ["fp64", "fp32"])
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (34, 10, 6, 14)], ids=lambda d: "x".join(map(str, d)))
+def test_server_counts_what_an_engine_holds(sloppy, dims):
+    """A server's account of an engine: per slot the fields, three arrays of
+    partial sums of 4 per block (the second lattice needs 184 blocks, for the
+    z-slabs of a lane pair per site) and the scalars."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0905_3331_amd import tmq
+
+    vh = int(np.prod(dims)) // 2
+    blocks = {(4, 4, 4, 4): 8, (34, 10, 6, 14): 184}[dims]
+    want = 3 * (slot_fields(sloppy, "reliable") * vh + 3 * 4 * blocks * 8 + 7 * 8 + 8 * 4)
+    o = tmq.solver_opts(tol=1e-3, sloppy=sloppy, sloppy_link="fp32")
+    p = tmq.params(0.1632, 0.01, (1.0, 0.0, 0.0, 0.0))
+    U = torch.from_numpy(synth.random_gauge(dims, seed=422)).to("cuda")
+    b = torch.ones(vh, 4, 3, dtype=torch.complex128, device="cuda")
+    torch.cuda.synchronize()
+    with tmq.Server(max_batch=3) as srv:
+        lid = srv.add_lattice(dims, U)
+        assert srv.wait(srv.submit(lid, p, b, o), timeout=60)[1].status == 0
+        st = srv.stats()
+    assert st["peak_bytes"] == want, (st["peak_bytes"], want)
