@@ -34,13 +34,13 @@ namespace tmq {
 constexpr int SPLIT_SITES = 64;    // sites per block
 constexpr int SPLIT_THREADS = 512;  // eight wavefronts
 
-// which operands are canonical complex128 buffers: the input, the own-site
-// field, the output; and whether these hold the whole lattice
 // EP_CG with alpha formed from the partials of <p, A p> (SplitArgs::pap; an
 // instantiation of its own: the registers it takes cost the others 0.7 % of an
 // FP64 solve at 24^3x48)
 constexpr int EP_CG_OWN = 4;
 
+// which operands are canonical complex128 buffers: the input, the own-site
+// field, the output; and whether these hold the whole lattice
 enum SplitCan { CAN_IN = 1, CAN_SELF = 2, CAN_OUT = 4, CAN_FULL = 8 };
 
 template <class SP, class LK>

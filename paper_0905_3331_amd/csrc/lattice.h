@@ -153,25 +153,25 @@ int hop(Lattice *L, int out_par, const FieldDesc &in, const FieldDesc &self, con
         const LinkDesc &lk, const OpParams &op, int epi, int sign, const RhsList &rl, double *partial,
         const CgScalars *scal, hipStream_t st, const CgFields *cg = nullptr);
 
-// Qhat^{sign} in -> out (odd fields), tmp_e an even work field; partial: |out|^2 per block
 // out = Qhat in on canonical odd-site buffers: fi and fo describe them as
 // canonical where the half-sweeps read and write them in place, and are work
 // fields for conversion passes where not
 int apply_Qhat_canonical(Lattice *L, const OpParams &op, int sign, const double2 *in, double2 *out,
                          const FieldDesc &fi, const FieldDesc &fo, const FieldDesc &te, const LinkDesc &lk,
                          hipStream_t st);
+// Qhat^{sign} in -> out (odd fields), tmp_e an even work field; partial: |out|^2 per wavefront
 int apply_Qhat(Lattice *L, const OpParams &op, int sign, const FieldDesc &in, const FieldDesc &out,
                const FieldDesc &tmp_e, const LinkDesc &lk, const RhsList &rl, double *partial,
                const CgScalars *scal, hipStream_t st);
-// Qhat^+ applied to in (odd), fused with the CG update of the vectors of cg
-// (r -= alpha Qhat^+ in ; x += alpha p, alpha from scal); partial: |r|^2 per block
+// Qhat^+ applied to in (odd), fused with the CG update of the residual of cg
+// (r -= alpha Qhat^+ in, alpha from scal or from cg's partials); partial: |r|^2 per wavefront
 int apply_Qhat_cg(Lattice *L, const OpParams &op, const FieldDesc &in, const FieldDesc &tmp_e, const LinkDesc &lk,
                   const RhsList &rl, const CgFields &cg, double *partial, const CgScalars *scal, hipStream_t st);
-// r = b - Qhat^+ Qhat^- x (FP64 or any one format) with |r|^2 per block in partial
+// r = b - Qhat^+ Qhat^- x (FP64; r stored in its own format) with |r|^2 per wavefront in partial
 int residual_QhatQhat(Lattice *L, const OpParams &op, const FieldDesc &x, const FieldDesc &b, const FieldDesc &r,
                       const FieldDesc &tmp_e, const FieldDesc &tmp_o, const LinkDesc &lk, const RhsList &rl,
                       double *partial, hipStream_t st);
-// Qhat^+ Qhat^- in -> out; partial receives |Qhat^- in|^2 per block
+// Qhat^+ Qhat^- in -> out; partial receives |Qhat^- in|^2 per wavefront
 int apply_QhatQhat(Lattice *L, const OpParams &op, const FieldDesc &in, const FieldDesc &out,
                    const FieldDesc &tmp_e, const FieldDesc &tmp_o, const LinkDesc &lk, const RhsList &rl,
                    double *partial, const CgScalars *scal, hipStream_t st);
