@@ -42,7 +42,7 @@ if ROOT not in sys.path:
 KERNEL_SOURCES = ("hop_impl.h", "hop.hip", "hop_f64.hip", "hop_f32.hip", "hop_f16.hip", "hop_b16.hip",
                   "hop16_f16.hip", "hop16_b16.hip", "hop_split.h", "hop_split_nd.h",
                   "hop_split_f64.hip", "hop_split_f32.hip", "hop_split_f16.hip", "hop_split_b16.hip",
-                  "fields.h", "spin.h", "views.h", "kernels.h", "devutil.h", "fastdiv.h")
+                  "fields.h", "spin.h", "views.h", "kernels.h", "devutil.h", "fastdiv.h", "hop_grid.h")
 
 
 def code_text(src: str) -> str:
