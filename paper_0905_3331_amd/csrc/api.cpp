@@ -78,9 +78,8 @@ bool overlap(const double *a, const double *b, size_t bytes)
 }
 
 // Makes fi and fo the caller's canonical buffers where the half-sweeps of Qhat
-// can read and write them; true if that is both of them.  Overlapping buffers
-// keep the conversion of the input.
-bool qhat_in_place(const Lattice *L, const OpParams &op, int prec, const LinkDesc &lk, const double *in, double *out,
+// can read and write them.  Overlapping buffers keep the conversion of the input.
+void qhat_in_place(const Lattice *L, const OpParams &op, int prec, const LinkDesc &lk, const double *in, double *out,
                    FieldDesc *fi, FieldDesc *fo)
 {
     const long vh = L->g.vh;
@@ -88,7 +87,6 @@ bool qhat_in_place(const Lattice *L, const OpParams &op, int prec, const LinkDes
     const bool co = hop_writes_canonical(L->g, prec, lk.fmt, op);
     if (ci) *fi = canonical_desc(prec, in, vh, LAY_CANONICAL);
     if (co) *fo = canonical_desc(prec, out, vh, LAY_CANONICAL);
-    return ci && co;
 }
 
 // odd-site Qhat on device canonical buffers
@@ -98,11 +96,13 @@ int qhat_dev(Lattice *L, const tmq_params *p, int sign, int prec, const double *
     FieldDesc fi, fo, te;
     const LinkDesc lk = lattice_links(L, link_fmt_for(L, prec, prec == TMQ_FP32 ? P32 : P16));
     const OpParams op = make_op(L, p, 1);
-    if (!qhat_in_place(L, op, prec, lk, in, out, &fi, &fo)) {
-        if (!fi.layout) TMQ_TRY(work_field(L, "op_in", prec, vh, &fi));
-        if (!fo.layout) TMQ_TRY(work_field(L, "op_out", prec, vh, &fo));
-    }
+    // (the work fields of any call in this precision, also where this one does
+    // without them: the next may be captured, where nothing can be allocated, and
+    // overlap its buffers or have other phases, on which the 16-bit kernel depends)
+    TMQ_TRY(work_field(L, "op_in", prec, vh, &fi));
+    if (!hop_takes_split(L->g, prec, lk.fmt)) TMQ_TRY(work_field(L, "op_out", prec, vh, &fo));
     TMQ_TRY(work_field(L, "op_te", prec, vh, &te));
+    qhat_in_place(L, op, prec, lk, in, out, &fi, &fo);
     return apply_Qhat_canonical(L, op, sign, (const double2 *)in, (double2 *)out, fi, fo, te, lk, st);
 }
 
@@ -318,13 +318,12 @@ int tmq_apply_QhatQhat_dev(tmq_lattice *lat, const tmq_params *p, const double *
     const LinkDesc lk = lattice_links(L, link_fmt_for(L, P64, P64));
     TMQ_TRY(work_field(L, "op_te", P64, vh, &te));
     TMQ_TRY(work_field(L, "op_to", P64, vh, &to));
+    TMQ_TRY(work_field(L, "op_in", P64, vh, &fi));  // (as for Qhat)
     // (the input is read for the last time before the output is written)
-    if (hop_reads_canonical(L->g, P64, lk.fmt, vh)) {
+    if (hop_reads_canonical(L->g, P64, lk.fmt, vh))
         fi = canonical_desc(P64, in, vh, LAY_CANONICAL);
-    } else {
-        TMQ_TRY(work_field(L, "op_in", P64, vh, &fi));
+    else
         TMQ_HIP(launch_from_canonical((const double2 *)in, fi, st));
-    }
     return apply_QhatQhat(L, make_op(L, p, 1), fi, canonical_desc(P64, out, vh, LAY_CANONICAL), te, to, lk, rhs_all(1),
                           nullptr, nullptr, st);
 }
@@ -343,12 +342,13 @@ int tmq_apply_Q_full_dev(tmq_lattice *lat, const tmq_params *p, int sign, const 
     const OpParams op = make_op(L, p, 1);
     const LinkDesc lk = lattice_links(L, link_fmt_for(L, P64, P64));
     // (if the buffers overlap, the second half-sweep would read what the first has written)
-    FieldDesc fi = canonical_desc(P64, in, n, LAY_CANONICAL_FULL);
+    FieldDesc fi;
     const FieldDesc fo = canonical_desc(P64, out, n, LAY_CANONICAL_FULL);
-    if (!hop_reads_canonical(L->g, P64, lk.fmt, n) || overlap(in, out, (size_t)n * 12 * 16)) {
-        TMQ_TRY(work_field(L, "full_in", P64, n, &fi));
+    TMQ_TRY(work_field(L, "full_in", P64, n, &fi));  // (as for Qhat)
+    if (hop_reads_canonical(L->g, P64, lk.fmt, n) && !overlap(in, out, (size_t)n * 12 * 16))
+        fi = canonical_desc(P64, in, n, LAY_CANONICAL_FULL);
+    else
         TMQ_HIP(launch_full_from_canonical(L->g, (const double2 *)in, fi, st));
-    }
     return apply_Q_full(L, op, sign, fi, fo, lk, rhs_all(1), st);
 }
 
