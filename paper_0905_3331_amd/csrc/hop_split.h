@@ -19,9 +19,10 @@
 // flight at once, 56 registers in FP32 and 108 in FP64 leave 8 and 4
 // wavefronts per SIMD, and for the same bytes in flight a third as many sites,
 // so more of a site's neighbours are still in the XCD's L2 when they are used
-// again (FP64 K1 at 32^3x64 reads 1.11 GB instead of 1.36, 1.01 without any
-// re-read).  K1 in us, hop_kernel -> here: FP64 8^3x16 9.8 -> 4.9, 24^3x48
-// 83.4 -> 71.5, 32^3x64 223 -> 213 (5.7 TB/s of operands, HBM-bound); FP32
+// again (FP64 K1 at 32^3x64 reads 1.07-1.11 GB instead of 1.36, 1.01 without
+// any re-read).  K1 in us, hop_kernel -> here on one box: FP64 8^3x16 9.8 ->
+// 4.9, 24^3x48 83.4 -> 71.5, 32^3x64 223 -> 213 (5.7 TB/s of operands,
+// HBM-bound; 203-212 on others); FP32
 // 7.9 -> 4.0, 42.8 -> 37.6, 109 -> 104; FP16 8^3x16 6.0 -> 4.0.
 // The exchange costs vector instructions and LDS traffic, which the 16-bit
 // half-sweep, bound by its vector instructions once the chip is full, cannot

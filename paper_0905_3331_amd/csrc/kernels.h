@@ -175,9 +175,10 @@ inline bool hop_takes_split(const Geom &g, int prec, int link_fmt)
 // of <p, A p> itself (SC_ALPHA_BETA follows it): a launch and the wait between
 // two kernels less per iteration, for as many reads of the partials as there are
 // blocks.  A wavefront takes 64 of them, so a block's eight take 512.  Solves
-// with a launch of its own -> here, us: FP32 8^3x16 (16 blocks) 1120 -> 1058,
-// 16^3x32 (256) 2217 -> 2160; FP64 1344 -> 1296, 3216 -> 3203; with 512 blocks
-// (16^3x64) FP32 3501 -> 3483, FP64 the same, so the line is drawn there.
+// repeated on the same inputs, a launch of its own -> here, us: FP32 8^3x16 (16
+// blocks) 1138 -> 1069, 16^3x32 (256) 2207 -> 2154; FP64 1197 -> 1145, 3240 ->
+// 3170; with 512 blocks (16^3x64) FP32 3489 -> 3460, FP64 5660 -> 5630, half a
+// per cent, so the line is drawn there.
 inline bool hop_sums_alpha(const Geom &g, int prec, int link_fmt, int nparts)
 {
     return hop_takes_split(g, prec, link_fmt) && nparts <= 512;
