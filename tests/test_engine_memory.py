@@ -1,5 +1,7 @@
 """Device memory of the CG engines: the fields that a slot is said to hold, and
 the memory that a batch takes for them."""
+import gc
+
 import numpy as np
 import pytest
 
@@ -46,6 +48,7 @@ def test_memory_of_a_batch(sloppy):
     bs = [torch.ones(vh, 4, 3, dtype=torch.complex128, device="cuda") for _ in range(n)]
     xs = [torch.zeros_like(b) for b in bs]
     lat.solve(p, bs[0], o)  # (code and the engine of one slot, which the batch replaces)
+    gc.collect()  # (lattices that other tests left)
     torch.cuda.synchronize()
     free0 = torch.cuda.mem_get_info()[0]
     lat.solve_batch([p] * n, bs, o, xs)
